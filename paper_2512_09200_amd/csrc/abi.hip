@@ -730,9 +730,9 @@ static size_t mlp_bwd_ws(const lattice_mlp_desc* d, int B) {
     GemmArgs g;
     g.dt = dt_of(d->dtype);
     g.max_splits = MLP_MAX_SPLITS;
-    g.M = L.out_dim; g.N = L.in_dim; g.K = B;
+    g.M = L.out_dim; g.N = L.in_dim; g.K = B; g.ta = g.tb = 1;  // mlp_layer_wgrad's product
     s = std::max(s, gemm_workspace(g));
-    g.M = B; g.N = L.in_dim; g.K = L.out_dim;
+    g.M = B; g.N = L.in_dim; g.K = L.out_dim; g.ta = 0;         // mlp_layer_dgrad's
     s = std::max(s, gemm_workspace(g));
     s = std::max(s, colsum_workspace(B, L.out_dim));
     if (swish_layer(d, i)) s = std::max(s, swishrn_gain_workspace(B, L.out_dim));
@@ -922,8 +922,8 @@ static hipError_t mlp_layer_wgrad(const lattice_mlp_desc* d, int i, int B, const
       w.gk = 1;
       w.gsC = (int64_t)L.out_dim * L.in_dim;
     }
-    // bf16: db is the row sum of A = gᵀ, taken by the same GEMM
-    if (dt == DT_BF16 && L.db) {
+    // db is the row sum of A = gᵀ, taken by the same GEMM
+    if (L.db) {
       w.rowsum = L.db;
       db_done = true;
     }

@@ -52,6 +52,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_epi.h"
 #include "kernels.h"
 #include "swishrn.h"
 
@@ -61,40 +62,6 @@ constexpr int GBM = 128, GBN = 128, GBK = 64, GPAD = 8, GLD = GBK + GPAD;
 constexpr int CLD = GBN + 4;  // fp32 row stride of the staged C tile
 constexpr size_t GEMM_LDS = (size_t)2 * (GBM + GBN) * GLD * sizeof(uint16_t);  // 73,728 B
 static_assert((size_t)GBM * CLD * sizeof(float) <= GEMM_LDS, "C staging must fit the operand stages");
-
-struct Epi {
-  const float* bias;    // [N] or null
-  int relu;
-  const void* mask;     // activation whose sign gates the output, or null
-  DType mask_dt;
-  int64_t ldm, s_mask;
-  const float* addend;  // + addend[m*ld_add + n] (fp32) or null
-  int64_t ld_add, s_add;
-  int accumulate;       // + the existing (fp32) C
-  // BlockNorm / SwishRN (kernels instantiated with NORM = gate): gain [2, N],
-  // pre [M, ldp] (C's dtype), rinv [M, nblk]
-  const float* gain;
-  float eps;
-  void* pre;
-  int64_t ldp;
-  float* rinv;
-  int nblk;
-};
-
-template <typename CT>
-__device__ inline void epi_store(CT* C, int64_t ldc, int row, int col, float v, const Epi& e,
-                                 int64_t bz) {
-  if (e.bias) v += e.bias[col];
-  if (e.addend) v += e.addend[bz * e.s_add + (int64_t)row * e.ld_add + col];
-  if (e.accumulate) v += ld(C + (int64_t)row * ldc + col);
-  if (e.relu) v = v > 0.f ? v : 0.f;
-  if (e.mask) {
-    const int64_t mi = bz * e.s_mask + (int64_t)row * e.ldm + col;
-    float g = e.mask_dt == DT_BF16 ? bf2f(((const bf16_t*)e.mask)[mi]) : ((const float*)e.mask)[mi];
-    v = g > 0.f ? v : 0.f;
-  }
-  st(C + (int64_t)row * ldc + col, v);
-}
 
 __device__ inline void ld8f(const float* p, float* v) {
   const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
@@ -942,36 +909,6 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(
   }
 }
 
-// Sum of the splits' partials in split order; the loads of 16 splits are
-// issued before their adds (a split's partial is a separate [M, N] slice, so
-// a plain loop would wait for one load at a time).
-__device__ inline float sum_splits(const float* __restrict__ p, int splits, int64_t stride) {
-  float s = 0.f;
-  int z = 0;
-  for (; z + 16 <= splits; z += 16) {
-    float v[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) v[q] = p[(int64_t)(z + q) * stride];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) s += v[q];
-  }
-  for (; z < splits; ++z) s += p[(int64_t)z * stride];
-  return s;
-}
-
-template <typename CT>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial,
-                                                            int splits, int M, int N,
-                                                            CT* __restrict__ C, int64_t ldc,
-                                                            Epi epi, const float* __restrict__ rs_partial,
-                                                            float* __restrict__ rowsum) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (rowsum && i < M) rowsum[i] = sum_splits(rs_partial + i, splits, M);
-  if (i >= (int64_t)M * N) return;
-  const int row = (int)(i / N), col = (int)(i % N);
-  epi_store<CT>(C, ldc, row, col, sum_splits(partial + i, splits, (int64_t)M * N), epi, 0);
-}
-
 // --- large products: block tile 256x256, 4 waves of 128x128 (4x4 fragments) or 8 of 128x64 ---
 // Twice the MFMA work per byte read from LDS of the 128x128 kernel (whose
 // 64x64 wave tiles keep the LDS port as busy as the matrix cores), for
@@ -1217,51 +1154,6 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_big_kernel(Opnd A, Opnd Bm, C
   }
 }
 
-// --- fp32 VALU GEMM (fp32 workloads): 64x64 tile, 4x4 per thread, any layout ---
-template <typename CT>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda,
-                                                       int ta, const float* __restrict__ Bm,
-                                                       int64_t ldb, int tb, CT* __restrict__ C,
-                                                       int64_t ldc, int M, int N, int K,
-                                                       Epi epi) {
-  constexpr int T = 64, KS = 16;
-  __shared__ float As[KS][T + 1];
-  __shared__ float Bs[KS][T + 1];
-  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += KS) {
-    for (int e = threadIdx.x; e < KS * T; e += 256) {
-      const int kk = e / T, r = e % T;
-      const int gk = k0 + kk;
-      const int gm = m0 + r, gn = n0 + r;
-      As[kk][r] = (gm < M && gk < K) ? (ta ? A[(int64_t)gk * lda + gm] : A[(int64_t)gm * lda + gk]) : 0.f;
-      Bs[kk][r] = (gn < N && gk < K) ? (tb ? Bm[(int64_t)gk * ldb + gn] : Bm[(int64_t)gn * ldb + gk]) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
-      if (row < M && col < N) epi_store<CT>(C, ldc, row, col, acc[i][j], epi, 0);
-    }
-}
-
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // Split-K factor by an estimated time: ceil(blocks / 512) waves (two blocks
@@ -1271,6 +1163,7 @@ static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // takes 26 us at 8 splits and 32 us at 16), so any factor (not only powers
 // of two) that balances the waves is considered; ties keep fewer splits.
 int gemm_splits(const GemmArgs& g) {
+  if (g.dt == DT_F32) return gemm_f32_splits(g);
   if (g.dt != DT_BF16 || g.batch > 1 || g.max_splits <= 1) return 1;
   const int64_t tiles = (int64_t)cdiv(g.M, GBM) * cdiv(g.N, GBN);
   double best = 0.0;
@@ -1294,12 +1187,6 @@ int gemm_splits(const GemmArgs& g) {
 size_t gemm_workspace(const GemmArgs& g) {
   int splits = gemm_splits(g);
   return splits > 1 ? (size_t)splits * ((size_t)g.M * g.N + g.M) * sizeof(float) : 0;
-}
-
-static Epi make_epi(const GemmArgs& g) {
-  return Epi{g.bias,   g.relu,     g.mask, g.mask_dt, g.ldm,  g.s_mask, g.addend,
-             g.ld_add, g.s_add,    g.accumulate,      g.gain, g.eps,    g.pre,
-             g.ldp,    g.rinv,     g.nblk};
 }
 
 static bool a16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -1482,8 +1369,8 @@ hipError_t gemm(const GemmArgs& g0, void* ws, hipStream_t st) {
     set_error("accumulating GEMM needs an fp32 output");
     return hipErrorInvalidValue;
   }
-  if (g.rowsum && (g.dt != DT_BF16 || g.batch > 1)) {
-    set_error("GEMM row sums: bf16 and not batched only");
+  if (g.rowsum && g.batch > 1) {
+    set_error("GEMM row sums: not batched only");
     return hipErrorInvalidValue;
   }
   if (g.norm_gate) {
@@ -1510,16 +1397,7 @@ hipError_t gemm(const GemmArgs& g0, void* ws, hipStream_t st) {
     set_error("fp32 GEMM: batching / K segmentation not supported");
     return hipErrorInvalidValue;
   }
-  dim3 grid(cdiv(g.N, 64), cdiv(g.M, 64));
-  Epi epi = make_epi(g);
-  if (g.c_dt == DT_F32)
-    gemm_f32_kernel<float><<<grid, 256, 0, st>>>((const float*)g.A, g.lda, g.ta, (const float*)g.B,
-                                                 g.ldb, g.tb, (float*)g.C, g.ldc, g.M, g.N, g.K, epi);
-  else
-    gemm_f32_kernel<bf16_t><<<grid, 256, 0, st>>>((const float*)g.A, g.lda, g.ta, (const float*)g.B,
-                                                  g.ldb, g.tb, (bf16_t*)g.C, g.ldc, g.M, g.N, g.K, epi);
-  LAT_LAUNCH_CHECK();
-  return hipSuccess;
+  return gemm_f32(g, (float*)ws, st);
 }
 
 // --- deterministic column sums: out[n] = sum_m G[m*ld + n] (bias gradients) ---

@@ -62,7 +62,7 @@ struct GemmArgs {
   int64_t sA = 0, sB = 0, sC = 0;
   int kseg = 0;                // K segmentation: k -> (k / kseg) * ks + k % kseg (0: none)
   int64_t ksA = 0, ksB = 0;
-  float* rowsum = nullptr;     // bf16, not batched: rowsum[m] = sum_k A[m][k] (fp32, k order)
+  float* rowsum = nullptr;     // not batched (fp32: ta only): rowsum[m] = sum_k A[m][k] (fp32, k order)
   // BlockNorm epilogue (SwishRN over 128-column groups): gate 1 = sigmoid,
   // 2 = hard sigmoid; gain [2, N] (g_a; g_b); pre [M, ldp] receives h =
   // acc + bias in C's dtype, rinv [M, nblk = ceil(N / 128)] each group's
@@ -84,6 +84,8 @@ struct GemmArgs {
   int nblk = 0;
 };
 int gemm_splits(const GemmArgs& g);
+int gemm_f32_splits(const GemmArgs& g);
+hipError_t gemm_f32(const GemmArgs& g, float* ws, hipStream_t s);  // gemm_f32.hip; through gemm()
 size_t gemm_workspace(const GemmArgs& g);
 hipError_t gemm(const GemmArgs& g, void* ws, hipStream_t s);
 size_t colsum_workspace(int M, int N);
