@@ -805,6 +805,12 @@ __global__ __launch_bounds__(256) void sum_parts_grouped_kernel(const float* __r
 
 constexpr int FM_MFMA_BLOCKS = 256;
 
+hipError_t sum_parts(const float* part, int parts, int64_t len, float* out, hipStream_t s) {
+  sum_parts_grouped_kernel<<<cdiv(len, 32), 256, 0, s>>>(part, parts, len, out);
+  LAT_LAUNCH_CHECK();
+  return hipSuccess;
+}
+
 bool fm_mfma_supported(int n, int d, int k) {
   if (n < 1) return false;
   // up to three (k = 32) or two (k = 64) tiles of 32 rows, plus a head row
@@ -876,10 +882,7 @@ static hipError_t fm_mfma_launch(bool fwd, const void* X, const void* W, int B, 
       LAT_LAUNCH_CHECK();
     }
   }
-  const int64_t len = (int64_t)n * K;
-  sum_parts_grouped_kernel<<<cdiv(len, 32), 256, 0, s>>>(part, B > 0 ? bblocks : 0, len, dW);
-  LAT_LAUNCH_CHECK();
-  return hipSuccess;
+  return sum_parts(part, B > 0 ? bblocks : 0, (int64_t)n * K, dW, s);
 }
 
 hipError_t fm_mfma(bool fwd, const void* X, const void* W, int B, int n, int d, int k, void* out,

@@ -183,15 +183,6 @@ __global__ __launch_bounds__(256) void fm_bwd_kernel(const T* __restrict__ X, co
   }
 }
 
-__global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict__ part, int parts,
-                                                        int64_t len, float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= len) return;
-  float s = 0.f;
-  for (int p = 0; p < parts; ++p) s += part[(int64_t)p * len + i];
-  out[i] = s;
-}
-
 constexpr int FM_BWD_BLOCKS = 512;
 
 size_t fm_bwd_workspace(int n, int k) { return (size_t)FM_BWD_BLOCKS * n * k * sizeof(float); }
@@ -204,6 +195,8 @@ static hipError_t set_lds(const void* fn, size_t bytes) {
 hipError_t dot_fwd(DType dt, const void* X, int B, int n, int d, void* out, int64_t ostride,
                    int emit0, hipStream_t s) {
   if (B == 0) return hipSuccess;
+  if (dot_f32_supported(n, d, X))
+    return dot_f32(dt, true, X, B, n, d, out, ostride, emit0, nullptr, 0, nullptr, s);
   const size_t lds = (size_t)n * (d + 1) * 4;
   if (dt == DT_BF16) {
     auto fn = dot_fwd_kernel<bf16_t>;
@@ -221,6 +214,8 @@ hipError_t dot_fwd(DType dt, const void* X, int B, int n, int d, void* out, int6
 hipError_t dot_bwd(DType dt, const void* X, int B, int n, int d, const void* dout,
                    int64_t dstride, int emit0, void* dX, hipStream_t s) {
   if (B == 0) return hipSuccess;
+  if (dot_f32_supported(n, d, X))
+    return dot_f32(dt, false, X, B, n, d, nullptr, 0, emit0, dout, dstride, dX, s);
   const size_t lds = ((size_t)n * (d + 1) + (size_t)n * (n + 1)) * 4;
   if (dt == DT_BF16) {
     auto fn = dot_bwd_kernel<bf16_t>;
@@ -243,6 +238,7 @@ size_t fm_lds_bytes(int n, int d, int k) {
 hipError_t fm_fwd(DType dt, const void* X, const void* W, int B, int n, int d, int k, void* out,
                   int64_t ostride, int emit0, hipStream_t s) {
   if (B == 0) return hipSuccess;
+  if (fm_f32_supported(n, d, k, X)) return fm_fwd_f32(dt, X, W, B, n, d, k, out, ostride, emit0, s);
   const size_t lds = ((size_t)n * (d + 1) + (size_t)n * k + (size_t)d * (k + 1)) * 4;
   if (dt == DT_BF16) {
     auto fn = fm_fwd_kernel<bf16_t>;
@@ -260,6 +256,8 @@ hipError_t fm_fwd(DType dt, const void* X, const void* W, int B, int n, int d, i
 hipError_t fm_bwd(DType dt, const void* X, const void* W, int B, int n, int d, int k,
                   const void* dout, int64_t dstride, int emit0, const float* addend,
                   void* dX, DType dxt, float* dW, void* ws, hipStream_t s) {
+  if (B > 0 && !addend && dxt == dt && fm_f32_supported(n, d, k, X))
+    return fm_bwd_f32(dt, X, W, B, n, d, k, dout, dstride, emit0, dX, dW, ws, s);
   const int blocks = B < FM_BWD_BLOCKS ? (B > 0 ? B : 1) : FM_BWD_BLOCKS;
   const size_t lds = fm_lds_bytes(n, d, k);
   float* part = (float*)ws;
@@ -278,10 +276,7 @@ hipError_t fm_bwd(DType dt, const void* X, const void* W, int B, int n, int d, i
 #undef LAT_FMB
     LAT_LAUNCH_CHECK();
   }
-  const int64_t len = (int64_t)n * k;
-  sum_parts_kernel<<<cdiv(len, 256), 256, 0, s>>>(part, B > 0 ? blocks : 0, len, dW);
-  LAT_LAUNCH_CHECK();
-  return hipSuccess;
+  return sum_parts(part, B > 0 ? blocks : 0, (int64_t)n * k, dW, s);
 }
 
 }  // namespace lat

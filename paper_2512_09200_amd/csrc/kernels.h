@@ -131,7 +131,20 @@ hipError_t fm_bwd(DType dt, const void* X, const void* W, int B, int n, int d, i
                   const void* dout, int64_t dstride, int emit0, const float* addend,
                   void* dX, DType dxt, float* dW, void* ws, hipStream_t s);
 
+// interact_f32.hip (fp32 MFMA path of DOT and FM, fp32 or bf16 storage; taken by
+// dot_fwd .. fm_bwd where it is supported; fm_bwd_f32: ws as fm_bwd's)
+bool fm_f32_supported(int n, int d, int k, const void* X);
+hipError_t fm_fwd_f32(DType dt, const void* X, const void* W, int B, int n, int d, int k, void* out, int64_t ostride,
+                      int emit0, hipStream_t s);
+hipError_t fm_bwd_f32(DType dt, const void* X, const void* W, int B, int n, int d, int k, const void* dout,
+                      int64_t dstride, int emit0, void* dX, float* dW, void* ws, hipStream_t s);
+bool dot_f32_supported(int n, int d, const void* X);
+hipError_t dot_f32(DType dt, bool fwd, const void* X, int B, int n, int d, void* out, int64_t ostride, int emit0,
+                   const void* dout, int64_t dstride, void* dX, hipStream_t s);
+
 // fm_mfma.hip (bf16 MFMA path of the FM block)
+// out[i] = sum over p of part[p][i], in a fixed order
+hipError_t sum_parts(const float* part, int parts, int64_t len, float* out, hipStream_t s);
 bool fm_mfma_supported(int n, int d, int k);
 size_t fm_mfma_bwd_workspace(int n, int k);
 hipError_t fm_mfma(bool fwd, const void* X, const void* W, int B, int n, int d, int k, void* out,

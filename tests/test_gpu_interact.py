@@ -35,8 +35,29 @@ CASES = {
     "fm-bf16-n33-d128-k32-head-odd": ("fm", "bf16", 37, 33, 128, 32, True, False),
     "fm-bf16-n64-d128-k64": ("fm", "bf16", 45, 64, 128, 64, False, False),
     "fm-bf16-n40-d128-k32": ("fm", "bf16", 515, 40, 128, 32, False, False),
-    "fm-bf16-valu": ("fm", "bf16", 33, 10, 32, 16, False, False),       # VALU path (d=32)
+    "fm-bf16-valu": ("fm", "bf16", 33, 10, 32, 16, False, False),       # d = 32: fp32 MFMA path
     "fm-f32-small": ("fm", "f32", 50, 10, 32, 16, False, False),
+    # fp32 MFMA path: tile and contraction edges of n, d and the rank, one to
+    # eight dW tiles (split over d or not), more samples than resident blocks
+    "fm-f32-n65-d128-k32": ("fm", "f32", 300, 65, 128, 32, True, False),
+    "fm-f32-n1-d16-k1": ("fm", "f32", 5, 1, 16, 1, True, False),
+    "fm-f32-n33-d48-k17": ("fm", "f32", 37, 33, 48, 17, False, False),
+    "fm-f32-n96-d128-k33": ("fm", "f32", 19, 96, 128, 33, True, False),
+    "fm-f32-n128-d64-k40-many": ("fm", "f32", 600, 128, 64, 40, True, False),
+    "fm-f32-n20-d256-k16": ("fm", "f32", 40, 20, 256, 16, False, False),
+    "fm-bf16-n80-d128-k16-many": ("fm", "bf16", 700, 80, 128, 16, True, False),
+    "fm-bf16-n97-d64-k64": ("fm", "bf16", 61, 97, 64, 64, False, False),
+    "dot-f32-n1": ("dot", "f32", 9, 1, 32, 0, True, False),
+    "dot-f32-n2-d16": ("dot", "f32", 10, 2, 16, 0, False, False),
+    "dot-f32-n32-d64-odd": ("dot", "f32", 131, 32, 64, 0, True, False),
+    "dot-f32-n33-d96": ("dot", "f32", 41, 33, 96, 0, True, False),
+    "dot-f32-n97-d128": ("dot", "f32", 40, 97, 128, 0, True, False),
+    "dot-f32-n128-d64": ("dot", "f32", 20, 128, 64, 0, False, False),
+    "dot-bf16-n27-d32": ("dot", "bf16", 66, 27, 32, 0, True, False),
+    "dot-bf16-n40-d256": ("dot", "bf16", 30, 40, 256, 0, True, False),
+    # outside every MFMA path (d not a multiple of 16, rank over 64)
+    "dot-f32-n9-d24": ("dot", "f32", 20, 9, 24, 0, True, False),
+    "fm-f32-n12-d32-k70": ("fm", "f32", 20, 12, 32, 70, True, False),
 }
 
 
