@@ -23,6 +23,8 @@
 //              run cut by a range boundary leaves a partial sum
 //   fixup    : each run that crosses ranges sums its partials in range order
 // Work per wave is uniform whatever the Zipf skew of the rows.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -107,7 +109,7 @@ struct Frag {
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-constexpr int FWD_BAGS = 16;  // bags per wave in the forward
+constexpr int FWD_BAGS = 16;  // most bags per wave in the forward
 
 // S consecutive lookups of a chunk starting at chunk row s0 (all inside the
 // chunk when CHECK is false): their table rows are loaded together, then
@@ -146,7 +148,7 @@ __device__ inline void fwd_group(int s0, int cnt, uint64_t emask, int grow, int 
   }
 }
 
-// One wave per FWD_BAGS consecutive bags (feature-major, so a wave's bags are
+// One wave per `per` (<= FWD_BAGS) consecutive bags (feature-major, so a wave's bags are
 // consecutive samples of one or two features).  The wave walks their lookups
 // in position order one table row per step: lane l holds bytes
 // [l*BPL, (l+1)*BPL) of the row, so bag ends are the same for every lane and
@@ -159,7 +161,7 @@ template <typename TT, typename XT, int BPL, bool MEAN, bool FULL>
 __global__ __launch_bounds__(256) void embbag_fwd_kernel(
     const TT* __restrict__ E, const int64_t* __restrict__ row_base,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ indices, int F, int B,
-    int dim, XT* __restrict__ X, int n_slots, int first_slot) {
+    int dim, XT* __restrict__ X, int n_slots, int first_slot, int per) {
   constexpr int EPL = BPL / (int)sizeof(TT);
   constexpr int S = BPL == 4 ? 32 : (BPL == 8 ? 16 : 8);
   const int lane = threadIdx.x & 63;
@@ -168,9 +170,9 @@ __global__ __launch_bounds__(256) void embbag_fwd_kernel(
   // control flow throughout.
   const int wave = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6));
   const int nbags = F * B;
-  const int b0 = wave * FWD_BAGS;
+  const int b0 = wave * per;
   if (b0 >= nbags) return;
-  const int nb = nbags - b0 < FWD_BAGS ? nbags - b0 : FWD_BAGS;
+  const int nb = nbags - b0 < per ? nbags - b0 : per;
   // lane k <= nb holds offsets[b0 + k]
   const int offv = lane <= nb ? offsets[b0 + lane] : 0;
   const int p_begin = __builtin_amdgcn_readlane(offv, 0);
@@ -254,10 +256,13 @@ static hipError_t embbag_fwd_t(const void* E, int dim, const int64_t* row_base,
   const int64_t bags = (int64_t)F * B;
   if (bags == 0) return hipSuccess;
   const int row_bytes = dim * (int)sizeof(TT);
-  const int grid = cdiv(cdiv(bags, FWD_BAGS), 4);
+  // 16 bags per wave amortise a wave's start; batches of too few bags for
+  // that to fill the chip (256 compute units x 16 waves) take 4
+  const int per = bags >= 4096 * FWD_BAGS ? FWD_BAGS : 4;
+  const int grid = cdiv(cdiv(bags, per), 4);
 #define LAT_FWD(BPLV, MV, FV)                                                              \
   embbag_fwd_kernel<TT, XT, BPLV, MV, FV><<<grid, 256, 0, s>>>(                           \
-      (const TT*)E, row_base, offsets, indices, F, B, dim, (XT*)X, n_slots, first_slot)
+      (const TT*)E, row_base, offsets, indices, F, B, dim, (XT*)X, n_slots, first_slot, per)
   if (row_bytes == 256) {
     if (mean) LAT_FWD(4, true, true); else LAT_FWD(4, false, true);
   } else if (row_bytes < 256) {
@@ -290,9 +295,26 @@ hipError_t embbag_fwd(const void* E, DType edt, int dim, const int64_t* row_base
 constexpr int SEG_THREADS = 256;
 constexpr int SEG_ITEMS = 16;
 constexpr int SEG_TILE = SEG_THREADS * SEG_ITEMS;
-// Sorted occurrences per wave in the segmented reduction.  Partial sums only
-// arise where a run crosses a multiple of RANGE.
-constexpr int RANGE = 256;
+// Sorted occurrences per wave in the segmented reduction (a range): 256, or 64
+// for batches too small to fill the chip with waves of 256.  Partial sums only
+// arise where a run crosses a range boundary.  A wave walks its range as one
+// chain of dependent loads, so below about 2M lookups (8192 waves of 256; the
+// chip holds 5120) shorter ranges are faster: 4.6K lookups 39 -> 13 us, 532K
+// lookups of 128-byte rows 43 -> 26 us; above it they only add partial sums.
+constexpr int RANGE_SHIFT = 8, RANGE_SHIFT_SMALL = 6;
+constexpr int64_t RANGE_SMALL_MAX = (int64_t)1 << 21;
+static int range_shift(int64_t n, bool coarse) {
+  return !coarse && n <= RANGE_SMALL_MAX ? RANGE_SHIFT_SMALL : RANGE_SHIFT;
+}
+static int64_t range_count(int64_t n, bool coarse) {
+  const int s = range_shift(n, coarse);
+  return (n + ((int64_t)1 << s) - 1) >> s;
+}
+// the most ranges of any batch of at most n lookups
+static int64_t range_count_max(int64_t n, bool coarse) {
+  const int64_t c = range_count(n, coarse);
+  return coarse || n <= RANGE_SMALL_MAX ? c : std::max(c, range_count(RANGE_SMALL_MAX, false));
+}
 
 // The keys of a tile's SEG_ITEMS stripes and of the positions before them,
 // loaded as straight-line code from clamped positions (n >= 1), so that all
@@ -309,24 +331,15 @@ __device__ inline void seg_load(const int* __restrict__ keys, int n, int64_t bas
   }
 }
 
-__device__ inline int block_sum_scan(int v, int* lds, int* total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int x = v;
+__device__ inline int seg_block_sum(int v, int* lds) {
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) lds[w] = x;
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
   __syncthreads();
-  int wb = 0, tot = 0;
-  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) {
-    if (i < w) wb += lds[i];
-    tot += lds[i];
-  }
-  __syncthreads();
-  *total = tot;
-  return wb + x - v;
+  int s = 0;
+#pragma unroll
+  for (int q = 0; q < SEG_THREADS / 64; ++q) s += lds[q];
+  return s;
 }
 
 __global__ __launch_bounds__(SEG_THREADS) void seg_count_kernel(const int* __restrict__ keys, int n,
@@ -341,49 +354,79 @@ __global__ __launch_bounds__(SEG_THREADS) void seg_count_kernel(const int* __res
     const int64_t k = base + (int64_t)i * SEG_THREADS + threadIdx.x;
     c += (k < n && (k == 0 || key[i] != prev[i])) ? 1 : 0;
   }
-  int tot;
-  block_sum_scan(c, lds, &tot);
+  const int tot = seg_block_sum(c, lds);
   if (threadIdx.x == 0) tile_counts[blockIdx.x] = tot;
+}
+
+// counts[g] = sum of the counts of group g's SEG_GROUP tiles
+constexpr int SEG_GROUP = 1024;
+__global__ __launch_bounds__(SEG_THREADS) void seg_group_kernel(const int* __restrict__ tile_counts, int tiles,
+                                                                int* __restrict__ group_counts) {
+  __shared__ int lds[SEG_THREADS / 64];
+  int c = 0;
+#pragma unroll
+  for (int i = 0; i < SEG_GROUP / SEG_THREADS; ++i) {
+    const int64_t t = (int64_t)blockIdx.x * SEG_GROUP + i * SEG_THREADS + threadIdx.x;
+    c += t < tiles ? tile_counts[t] : 0;
+  }
+  const int tot = seg_block_sum(c, lds);
+  if (threadIdx.x == 0) group_counts[blockIdx.x] = tot;
 }
 
 // Run starts of one tile, visited as SEG_ITEMS consecutive 256-position
 // stripes (coalesced); a stripe's starts are ranked by wave ballots.  Writes
-// the unique rows and run offsets, num_unique, and for every RANGE-aligned
-// position k the id of the run holding position k-1 (-1 at k = 0).
+// the unique rows and run offsets, num_unique, and for every position k that
+// starts a reduction range (k a multiple of 1 << rshift) the id of the run
+// holding position k-1 (-1 at k = 0).  The runs before the tile: the block
+// adds up the counts of the tiles before it itself (a scan would be one more
+// launch; a single pass with look-back measured 32-140 us against 20-24 us
+// for both kernels, its tickets and polls being atomics on few addresses), in
+// batches of many tiles the group sums first.
 __global__ __launch_bounds__(SEG_THREADS) void seg_write_kernel(
-    const int* __restrict__ keys, int n, const int* __restrict__ tile_base,
-    int* __restrict__ unique_rows, int* __restrict__ seg_offsets, int* __restrict__ num_unique,
-    int* __restrict__ range_ubefore) {
-  __shared__ int wsum[SEG_THREADS / 64];
+    const int* __restrict__ keys, int n, const int* __restrict__ tile_counts,
+    const int* __restrict__ group_counts, int rshift, int* __restrict__ unique_rows,
+    int* __restrict__ seg_offsets, int* __restrict__ num_unique, int* __restrict__ range_ubefore) {
+  constexpr int NWV = SEG_THREADS / 64;
+  __shared__ int wsum[SEG_ITEMS][NWV];
+  __shared__ int red[NWV];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  int run = tile_base[blockIdx.x];
-  const int64_t base = (int64_t)blockIdx.x * SEG_TILE;
-  int keyv[SEG_ITEMS], prev[SEG_ITEMS];
-  seg_load(keys, n, base, keyv, prev);
+  const int tile = blockIdx.x;
+  const int64_t base = (int64_t)tile * SEG_TILE;
+  int key[SEG_ITEMS], prev[SEG_ITEMS];
+  seg_load(keys, n, base, key, prev);
+  int before = 0;
+  const int g0 = group_counts ? tile / SEG_GROUP : 0;
+  for (int g = threadIdx.x; g < g0; g += SEG_THREADS) before += group_counts[g];
+  for (int t = g0 * SEG_GROUP + threadIdx.x; t < tile; t += SEG_THREADS) before += tile_counts[t];
+  uint32_t starts = 0;  // bit i: this thread's position of stripe i starts a run
+  uint64_t m[SEG_ITEMS];
 #pragma unroll
   for (int i = 0; i < SEG_ITEMS; ++i) {
     const int64_t k = base + (int64_t)i * SEG_THREADS + threadIdx.x;
-    const bool in = k < n;
-    const int key = keyv[i];
-    const int fl = in && (k == 0 || key != prev[i]) ? 1 : 0;
-    const uint64_t m = __ballot(fl);
-    if (lane == 0) wsum[w] = __popcll(m);
-    __syncthreads();
+    const bool fl = k < n && (k == 0 || key[i] != prev[i]);
+    starts |= (fl ? 1u : 0u) << i;
+    m[i] = __ballot(fl);
+    if (lane == 0) wsum[i][w] = __popcll(m[i]);
+  }
+  int run = seg_block_sum(before, red);  // (its barrier also covers wsum)
+#pragma unroll
+  for (int i = 0; i < SEG_ITEMS; ++i) {
+    const int64_t k = base + (int64_t)i * SEG_THREADS + threadIdx.x;
     int off = 0, tot = 0;
 #pragma unroll
-    for (int q = 0; q < SEG_THREADS / 64; ++q) {
-      off += q < w ? wsum[q] : 0;
-      tot += wsum[q];
+    for (int q = 0; q < NWV; ++q) {
+      off += q < w ? wsum[i][q] : 0;
+      tot += wsum[i][q];
     }
-    __syncthreads();
-    if (in) {
-      const int u = run + off + __popcll(m & lt) + fl - 1;  // run id of position k
+    if (k < n) {
+      const int fl = (starts >> i) & 1;
+      const int u = run + off + __popcll(m[i] & lt) + fl - 1;  // run id of position k
       if (fl) {
-        unique_rows[u] = key;
+        unique_rows[u] = key[i];
         seg_offsets[u] = (int)k;
       }
-      if (k % RANGE == 0) range_ubefore[k / RANGE] = u - fl;
+      if ((k & (((int64_t)1 << rshift) - 1)) == 0) range_ubefore[k >> rshift] = u - fl;
       if (k == n - 1) {
         num_unique[0] = u + 1;
         seg_offsets[u + 1] = n;
@@ -401,7 +444,7 @@ __global__ void set_empty_kernel(int* num_unique, int* seg_offsets) {
 // ---------------------------------------------------------------------------
 // backward: segmented reduction over the sorted occurrences (+ fused SGD)
 // ---------------------------------------------------------------------------
-// One wave per RANGE consecutive sorted occurrences.  The wave walks the
+// One wave per range of consecutive sorted occurrences.  The wave walks the
 // occurrences one dX row per step: lane l holds bytes [l*BPL, (l+1)*BPL) of
 // the row, so run starts and ends are the same for every lane and the
 // segmented sum is a single running fp32 accumulator per column, added to in
@@ -423,7 +466,10 @@ __global__ void set_empty_kernel(int* num_unique, int* seg_offsets) {
 // a buffer access, group positions are compile-time constants in full chunks,
 // and the table is addressed through a buffer resource based at the range's
 // first row whenever the range's rows span less than 4 GiB (EBUF).
-template <typename DT, typename ET, int BPL, bool MEAN, bool FULL, bool SGD>
+// ROLL (short ranges, small batches): the groups of a chunk as a loop instead
+// of unrolled code.  A launch that runs for some microseconds pays for every
+// kilobyte of code it fetches: 4.6K lookups took 39 us with 47 KB of it.
+template <typename DT, typename ET, int BPL, bool MEAN, bool FULL, bool SGD, bool ROLL>
 struct SegWave {
   static constexpr int EPL = BPL / (int)sizeof(DT);              // columns per lane
   static constexpr int S = BPL == 4 ? 32 : (BPL == 8 ? 16 : 8);  // rows in flight
@@ -493,21 +539,21 @@ struct SegWave {
     }
   }
 
-  // One group of S occurrences starting at chunk row s0 (s0 + S <= cnt when
+  // One group of SG occurrences starting at chunk row s0 (s0 + SG <= cnt when
   // CHECK is false).  Per lane (= chunk row): xoff, the byte offset of the
   // occurrence's dX row; erow, its table row as a byte offset into er (EBUF)
   // or as a row number (otherwise); scl, its bag's 1/length (MEAN).
-  template <bool CHECK, bool EBUF>
+  template <int SG, bool CHECK, bool EBUF>
   __device__ inline void group(const int s0, const int cnt, const uint64_t smask,
                                const uint64_t cmask, const uint64_t pmask, const int xoff,
                                const int erow, const float scl, const __amdgpu_buffer_rsrc_t er) {
-    Frag<DT, EPL> xf[S];
-    Frag<ET, EPL> ef[S];
-    // the group's run bits at positions 0 .. S-1 (constant-position tests below)
-    static_assert(S <= 32, "group masks are 32-bit");
+    Frag<DT, EPL> xf[SG];
+    Frag<ET, EPL> ef[SG];
+    // the group's run bits at positions 0 .. SG-1 (constant-position tests below)
+    static_assert(SG <= 32, "group masks are 32-bit");
     const uint32_t cm = (uint32_t)(cmask >> s0), pm = (uint32_t)(pmask >> s0);
 #pragma unroll
-    for (int i = 0; i < S; ++i) {
+    for (int i = 0; i < SG; ++i) {
       const int r = s0 + i;
       if (CHECK && r >= cnt) break;
       const int xr = __builtin_amdgcn_readlane(xoff, r);
@@ -529,13 +575,13 @@ struct SegWave {
       }
     }
     // the table row offsets are read from their lanes again at the update, and
-    // the run-end bits tested again, rather than held in 2*S scalar registers
+    // the run-end bits tested again, rather than held in 2*SG scalar registers
     // across the group (opaque copies the compiler cannot fold into the loads')
     int erow2 = erow;
     uint32_t cm2 = cm;
     if constexpr (SGD) asm volatile("" : "+v"(erow2), "+s"(cm2));
 #pragma unroll
-    for (int i = 0; i < S; ++i) {
+    for (int i = 0; i < SG; ++i) {
       const int r = s0 + i;
       if (CHECK && r >= cnt) break;
       if (MEAN) {
@@ -586,8 +632,7 @@ struct SegWave {
   __device__ inline void run(const int* __restrict__ skeys, const int* __restrict__ sbags, int n,
                              int r0, int rend, int B, int n_slots, int first_slot, int row_bytes,
                              const int32_t* __restrict__ offsets, int lane, int k_first,
-                             __amdgpu_buffer_rsrc_t er, int* __restrict__ part_uid,
-                             int* __restrict__ span_list, int* __restrict__ span_count) {
+                             __amdgpu_buffer_rsrc_t er, int* __restrict__ part_uid) {
     int prev_key = r0 > 0 ? __builtin_amdgcn_readfirstlane(skeys[r0 - 1]) : -1;
     int last_nxt = -1;
     int p0 = r0;
@@ -632,14 +677,26 @@ struct SegWave {
         if (MEAN) scl = 1.f / (float)(offsets[bag + 1] - offsets[bag]);
       }
       // full chunks: the groups unrolled with constant positions (not for the
-      // far-apart-rows fallback of the SGD path, which is rare)
-      if ((!SGD || EBUF) && cnt == 64) {
-#pragma unroll
-        for (int g = 0; g < 64 / S; ++g)
-          group<false, EBUF>(g * S, 64, smask, cmask, pmask, xoff, erow, scl, er);
-      } else {
+      // far-apart-rows fallback of the SGD path); only the batch's last chunk
+      // is a partial one
+      if (SGD && !EBUF) {
+#pragma unroll 1
         for (int s0 = 0; s0 < cnt; s0 += S)
-          group<true, EBUF>(s0, cnt, smask, cmask, pmask, xoff, erow, scl, er);
+          group<S, true, EBUF>(s0, cnt, smask, cmask, pmask, xoff, erow, scl, er);
+      } else if (cnt == 64) {
+        if constexpr (ROLL) {
+#pragma unroll 1
+          for (int g = 0; g < 64 / S; ++g)
+            group<S, false, EBUF>(g * S, 64, smask, cmask, pmask, xoff, erow, scl, er);
+        } else {
+#pragma unroll
+          for (int g = 0; g < 64 / S; ++g)
+            group<S, false, EBUF>(g * S, 64, smask, cmask, pmask, xoff, erow, scl, er);
+        }
+      } else {
+#pragma unroll 1
+        for (int s0 = 0; s0 < cnt; s0 += 8)
+          group<8, true, EBUF>(s0, cnt, smask, cmask, pmask, xoff, erow, scl, er);
       }
       started = started || smask != 0;
       prev_key = __builtin_amdgcn_readlane(key, cnt - 1);
@@ -651,30 +708,31 @@ struct SegWave {
       p0 = q0;
     }
     if (lane == 0) {
-      const bool touch_end = rend < n && last_nxt == prev_key;
-      part_uid[wave] = touch_end ? u_before : -1;
-      if (touch_end && started) span_list[atomicAdd(span_count, 1)] = wave;
+      // a run that starts in this range and goes on past it: the fixup's work
+      part_uid[wave] = started && rend < n && last_nxt == prev_key ? u_before : -1;
     }
   }
 };
 
-template <typename DT, typename ET, int BPL, bool MEAN, bool FULL, bool SGD>
+template <typename DT, typename ET, int BPL, bool MEAN, bool FULL, bool SGD, bool ROLL>
 __global__ __launch_bounds__(256) void seg_reduce_kernel(
     const int* __restrict__ skeys, const int* __restrict__ sbags, int n,
     const DT* __restrict__ dX, int B, int n_slots, int first_slot, int dim,
     const int32_t* __restrict__ offsets, const int* __restrict__ range_ubefore,
-    float* __restrict__ part, int* __restrict__ part_uid, int* __restrict__ span_list,
-    int* __restrict__ span_count, float* __restrict__ grad_rows, ET* __restrict__ E, float lr) {
-  using W = SegWave<DT, ET, BPL, MEAN, FULL, SGD>;
+    float* __restrict__ part, int* __restrict__ part_uid, float* __restrict__ grad_rows, ET* __restrict__ E, float lr,
+    int rshift) {
+  using W = SegWave<DT, ET, BPL, MEAN, FULL, SGD, ROLL>;
   const int lane = threadIdx.x & 63;
   // Each XCD takes a contiguous span of ranges, so the dX rows of one table's
   // occurrences stay in that XCD's L2 while it works through them.  Wave-
   // uniform values are made scalar explicitly: all control flow below is
   // uniform branching.
   const int wave = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6));
-  const int r0 = wave * RANGE;
-  if (r0 >= n) return;
-  const int rend = n - r0 < RANGE ? n : r0 + RANGE;
+  const int range = 1 << rshift;
+  const int64_t r0w = (int64_t)wave << rshift;
+  if (r0w >= n) return;
+  const int r0 = (int)r0w;
+  const int rend = n - r0 < range ? n : r0 + range;
   W w;
   w.wave = wave;
   w.dim = dim;
@@ -708,119 +766,124 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(
           reinterpret_cast<char*>(E) + (int64_t)k_first * w.erow_bytes, (short)0,
           (int)(uint32_t)span, BUF_RSRC_WORD3);
       w.template run<true>(skeys, sbags, n, r0, rend, B, n_slots, first_slot, row_bytes, offsets,
-                           lane, k_first, er, part_uid, span_list, span_count);
+                           lane, k_first, er, part_uid);
       return;
     }
   }
   w.template run<false>(skeys, sbags, n, r0, rend, B, n_slots, first_slot, row_bytes, offsets,
-                        lane, 0, w.dXr, part_uid, span_list, span_count);
+                        lane, 0, w.dXr, part_uid);
 }
 
-// One wave per run that crosses a range boundary: its partial sums (slot 1 of
-// the range where it starts, slot 0 of every later range it reaches) are
-// added in range order by S interleaved streams of dim/4 lanes each, then the
-// streams are combined in stream order; the total goes to the row gradient
-// and/or the SGD update.  A wave takes FIX_U runs per round and loads their
-// index chains (run -> its row id -> run end and table row), each stream's
-// first partial sum and the table values straight-line, all in flight
-// together (a round's positions past the last run re-read its first run, and
-// a null table reads the partials in its place; neither value is used), then
-// finishes the runs one by one: each run's arithmetic is that of a wave
-// taking it alone.
+// A run that crosses range boundaries: its partial sums (slot 1 of the range
+// where it starts, slot 0 of every later range it reaches) are added in range
+// order by S interleaved streams of dim/4 lanes each, then the streams are
+// combined in stream order; the total goes to the row gradient and/or the SGD
+// update.  A wave looks through `per` consecutive ranges for the runs that
+// start in them and cross their end (part_uid >= 0), and takes FIX_U of them
+// per round: their index chains (run id -> run end and table row), each
+// stream's first partial sum and the table values are loaded straight-line,
+// all in flight together (a round's positions past the last run re-read its
+// first run, and a null table reads the partials in its place; neither value
+// is used), then the runs are finished one by one: each run's arithmetic is
+// that of a wave taking it alone.
 constexpr int FIX_U = 4;
 template <typename ET>
 __global__ __launch_bounds__(256) void seg_fixup_kernel(
-    const int* __restrict__ span_list, const int* __restrict__ span_count,
-    const int* __restrict__ part_uid, const int* __restrict__ seg_offsets,
+    const int* __restrict__ part_uid, int ranges, int per, const int* __restrict__ seg_offsets,
     const int* __restrict__ unique_rows, const float* __restrict__ part, int dim,
-    float* __restrict__ grad_rows, ET* __restrict__ E, float lr) {
-  const int nspan = *span_count;
+    float* __restrict__ grad_rows, ET* __restrict__ E, float lr, int rshift) {
   const int lane = threadIdx.x & 63;
   const int CL = dim / 4;  // 4-column groups (dim % 8 == 0, dim <= 256)
   const int S = 64 / CL;   // streams
   const int cq = lane % CL, s = lane / CL;
   const bool act = s < S;
-  const int wave = blockIdx.x * 4 + (threadIdx.x >> 6), nwaves = gridDim.x * 4;
+  const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   const ET* eb = E ? E : reinterpret_cast<const ET*>(part);
-  for (int i0 = wave; i0 < nspan; i0 += FIX_U * nwaves) {
-    int c0[FIX_U], u[FIX_U], Q[FIX_U];
-    int64_t erow[FIX_U];
+  const int64_t rbeg = (int64_t)wave * per;
+  for (int64_t rb = rbeg; rb < rbeg + per && rb < ranges; rb += 64) {
+    const int64_t left = rbeg + per < ranges ? rbeg + per - rb : ranges - rb;
+    const int uid = lane < left ? part_uid[rb + lane] : -1;
+    uint64_t todo = __ballot(uid >= 0);
+    while (todo) {
+      int c0[FIX_U], u[FIX_U], Q[FIX_U];
+      int64_t erow[FIX_U];
+      const int first = __ffsll((unsigned long long)todo) - 1;
+      int cnt = 0;
 #pragma unroll
-    for (int t = 0; t < FIX_U; ++t) {
-      const int i = i0 + t * nwaves;
-      c0[t] = span_list[i < nspan ? i : i0];
-    }
+      for (int t = 0; t < FIX_U; ++t) {
+        const int l = todo ? __ffsll((unsigned long long)todo) - 1 : first;
+        cnt += todo ? 1 : 0;
+        todo &= todo - 1;
+        c0[t] = (int)rb + l;
+        u[t] = __builtin_amdgcn_readlane(uid, l);
+      }
 #pragma unroll
-    for (int t = 0; t < FIX_U; ++t) u[t] = part_uid[c0[t]];
+      for (int t = 0; t < FIX_U; ++t) {
+        Q[t] = ((seg_offsets[u[t] + 1] - 1) >> rshift) - c0[t] + 1;
+        erow[t] = E ? (int64_t)unique_rows[u[t]] * dim : 0;
+      }
+      // stream s's first partial sum (q = s; the run's first slot where the
+      // run does not reach it) and the run's table values
+      f32x4 a0[FIX_U];
+      float ev[FIX_U][4];
 #pragma unroll
-    for (int t = 0; t < FIX_U; ++t) {
-      Q[t] = (seg_offsets[u[t] + 1] - 1) / RANGE - c0[t] + 1;
-      erow[t] = E ? (int64_t)unique_rows[u[t]] * dim : 0;
-    }
-    // stream s's first partial sum (q = s; the run's first slot where the
-    // run does not reach it) and the run's table values
-    f32x4 a0[FIX_U];
-    float ev[FIX_U][4];
+      for (int t = 0; t < FIX_U; ++t) {
+        const int q = s < Q[t] ? s : 0;
+        const int64_t slot = q == 0 ? (int64_t)c0[t] * 2 + 1 : (int64_t)(c0[t] + q) * 2;
+        a0[t] = *reinterpret_cast<const f32x4*>(part + slot * dim + cq * 4);
 #pragma unroll
-    for (int t = 0; t < FIX_U; ++t) {
-      const int q = s < Q[t] ? s : 0;
-      const int64_t slot = q == 0 ? (int64_t)c0[t] * 2 + 1 : (int64_t)(c0[t] + q) * 2;
-      a0[t] = *reinterpret_cast<const f32x4*>(part + slot * dim + cq * 4);
+        for (int e = 0; e < 4; ++e) ev[t][e] = ld(eb + erow[t] + cq * 4 + e);
+      }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ev[t][e] = ld(eb + erow[t] + cq * 4 + e);
-    }
+      for (int t = 0; t < FIX_U; ++t) {
+        if (t >= cnt) break;  // wave-uniform
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+        if (act && s < Q[t]) {
+          a += a0[t];
+          int q = s + S;
+          for (; q + 3 * S < Q[t]; q += 4 * S) {
+            f32x4 v[4];
 #pragma unroll
-    for (int t = 0; t < FIX_U; ++t) {
-      if (i0 + t * nwaves >= nspan) break;  // wave-uniform
-      f32x4 a = {0.f, 0.f, 0.f, 0.f};
-      if (act && s < Q[t]) {
-        a += a0[t];
-        int q = s + S;
-        for (; q + 3 * S < Q[t]; q += 4 * S) {
-          f32x4 v[4];
+            for (int k = 0; k < 4; ++k) {
+              const int64_t slot = (int64_t)(c0[t] + q + k * S) * 2;
+              v[k] = *reinterpret_cast<const f32x4*>(part + slot * dim + cq * 4);
+            }
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int64_t slot = (int64_t)(c0[t] + q + k * S) * 2;
-            v[k] = *reinterpret_cast<const f32x4*>(part + slot * dim + cq * 4);
+            for (int k = 0; k < 4; ++k) a += v[k];
           }
-#pragma unroll
-          for (int k = 0; k < 4; ++k) a += v[k];
+          for (; q < Q[t]; q += S) a += *reinterpret_cast<const f32x4*>(part + (int64_t)(c0[t] + q) * 2 * dim + cq * 4);
         }
-        for (; q < Q[t]; q += S) a += *reinterpret_cast<const f32x4*>(part + (int64_t)(c0[t] + q) * 2 * dim + cq * 4);
-      }
-      f32x4 t4 = {0.f, 0.f, 0.f, 0.f};
-      for (int ss = 0; ss < S; ++ss) {
+        f32x4 t4 = {0.f, 0.f, 0.f, 0.f};
+        for (int ss = 0; ss < S; ++ss) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) t4[e] += __shfl(a[e], ss * CL + cq, 64);
-      }
-      if (s == 0) {
+          for (int e = 0; e < 4; ++e) t4[e] += __shfl(a[e], ss * CL + cq, 64);
+        }
+        if (s == 0) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int c = cq * 4 + e;
-          if (grad_rows) grad_rows[(int64_t)u[t] * dim + c] = t4[e];
-          if (E) st(E + erow[t] + c, ev[t][e] - lr * t4[e]);
+          for (int e = 0; e < 4; ++e) {
+            const int c = cq * 4 + e;
+            if (grad_rows) grad_rows[(int64_t)u[t] * dim + c] = t4[e];
+            if (E) st(E + erow[t] + c, ev[t][e] - lr * t4[e]);
+          }
         }
       }
     }
   }
 }
 
-__global__ void zero_int_kernel(int* p, int n) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-size_t embbag_bwd_workspace(int64_t nnz, int dim, int F) {
+// run bookkeeping: run starts per tile of keys and per group of tiles
+static int64_t run_words(int64_t n) { return (int64_t)cdiv(n, SEG_TILE) + cdiv(n, (int64_t)SEG_TILE * SEG_GROUP); }
+
+size_t embbag_bwd_workspace(int64_t nnz, int dim, int F, bool coarse) {
   const int64_t n = nnz > 0 ? nnz : 1;
-  const int64_t ranges = cdiv(n, RANGE);
+  const int64_t ranges = range_count_max(n, coarse);
   size_t s = 0;
   s += align256((size_t)n * 4);                        // sorted keys
   s += align256(radix_sort_segments_workspace(n, F));
-  s += align256((size_t)(cdiv(n, SEG_TILE) + 1) * 4);  // segment tile counts
-  s += 3 * align256((size_t)ranges * 4);               // range_ubefore, part_uid, span_list
-  s += align256(4);                                    // span_count
+  s += align256((size_t)run_words(n) * 4);
+  s += 2 * align256((size_t)ranges * 4);               // range_ubefore, part_uid
   s += align256((size_t)ranges * 2 * dim * 4);         // partial sums
   return s;
 }
@@ -829,29 +892,29 @@ template <typename DT, typename ET>
 static hipError_t embbag_bwd_reduce(const int* skeys, const int* sbags, int n, const void* dX,
                                     int B, int n_slots, int first_slot, int dim,
                                     const int32_t* offsets, int mean, const int* range_ubefore,
-                                    float* part, int* part_uid, int* span_list, int* span_count,
-                                    const int* seg_offsets, const int* unique_rows,
-                                    float* grad_rows, void* E, float lr, hipStream_t s,
+                                    float* part, int* part_uid, const int* seg_offsets, const int* unique_rows,
+                                    float* grad_rows, void* E, float lr, int rshift, hipStream_t s,
                                     void* const* ev) {
   // ev (optional): 4 events, begin / end of the reduction and of the fixup
   // (null entries are not recorded)
   auto record = [&](int i) -> hipError_t {
     return ev && ev[i] ? hipEventRecord((hipEvent_t)ev[i], s) : hipSuccess;
   };
-  const int ranges = cdiv(n, RANGE);
+  const int ranges = cdiv(n, (int64_t)1 << rshift);
   LAT_HIP_CHECK(record(0));
   const int row_bytes = dim * (int)sizeof(DT);
   const int grid = cdiv(ranges, 4);
+  const bool roll = rshift == RANGE_SHIFT_SMALL;
+#define LAT_SEG2(BPLV, MV, FV, SV, RV)                                                       \
+  seg_reduce_kernel<DT, ET, BPLV, MV, FV, SV, RV><<<grid, 256, 0, s>>>(                      \
+      skeys, sbags, n, (const DT*)dX, B, n_slots, first_slot, dim, offsets, range_ubefore,   \
+      part, part_uid, grad_rows, (ET*)E, lr, rshift)
 #define LAT_SEG(BPLV, MV, FV)                                                                \
   do {                                                                                      \
-    if (E)                                                                                  \
-      seg_reduce_kernel<DT, ET, BPLV, MV, FV, true><<<grid, 256, 0, s>>>(                   \
-          skeys, sbags, n, (const DT*)dX, B, n_slots, first_slot, dim, offsets, range_ubefore, \
-          part, part_uid, span_list, span_count, grad_rows, (ET*)E, lr);                    \
-    else                                                                                    \
-      seg_reduce_kernel<DT, ET, BPLV, MV, FV, false><<<grid, 256, 0, s>>>(                  \
-          skeys, sbags, n, (const DT*)dX, B, n_slots, first_slot, dim, offsets, range_ubefore, \
-          part, part_uid, span_list, span_count, grad_rows, (ET*)E, lr);                    \
+    if (E && roll) LAT_SEG2(BPLV, MV, FV, true, true);                                      \
+    else if (E) LAT_SEG2(BPLV, MV, FV, true, false);                                        \
+    else if (roll) LAT_SEG2(BPLV, MV, FV, false, true);                                     \
+    else LAT_SEG2(BPLV, MV, FV, false, false);                                              \
   } while (0)
   if (row_bytes == 256) {
     if (mean) LAT_SEG(4, true, true); else LAT_SEG(4, false, true);
@@ -863,14 +926,15 @@ static hipError_t embbag_bwd_reduce(const int* skeys, const int* sbags, int n, c
     if (mean) LAT_SEG(16, true, false); else LAT_SEG(16, false, false);
   }
 #undef LAT_SEG
+#undef LAT_SEG2
   LAT_LAUNCH_CHECK();
   LAT_HIP_CHECK(record(1));
   LAT_HIP_CHECK(record(2));
   // every wave resident (5 blocks of 4 waves per compute unit at the
-  // kernel's 88-96 VGPRs): each then takes its runs in rounds of FIX_U
-  const int fix_grid = grid < 1280 ? grid : 1280;
-  seg_fixup_kernel<ET><<<fix_grid, 256, 0, s>>>(span_list, span_count, part_uid, seg_offsets,
-                                                unique_rows, part, dim, grad_rows, (ET*)E, lr);
+  // kernel's 88-96 VGPRs), each with at least a round's worth of ranges
+  const int per = std::max(FIX_U, cdiv(ranges, 5120));
+  seg_fixup_kernel<ET><<<cdiv(cdiv(ranges, per), 4), 256, 0, s>>>(part_uid, ranges, per, seg_offsets, unique_rows, part,
+                                                                 dim, grad_rows, (ET*)E, lr, rshift);
   LAT_LAUNCH_CHECK();
   LAT_HIP_CHECK(record(3));
   return hipSuccess;
@@ -880,22 +944,20 @@ static hipError_t embbag_bwd_reduce(const int* skeys, const int* sbags, int n, c
 struct EmbBwdWs {
   int* skeys;
   void* sort_ws;
-  int *tile_counts, *range_ubefore, *part_uid, *span_list, *span_count;
+  int *tile_counts, *range_ubefore, *part_uid;
   float* part;
 };
-static EmbBwdWs emb_bwd_ws(void* ws, int64_t nnz, int dim, int F) {
+static EmbBwdWs emb_bwd_ws(void* ws, int64_t nnz, int dim, int F, bool coarse) {
   const int64_t n = nnz > 0 ? nnz : 1;
-  const int64_t ranges = cdiv(n, RANGE);
+  const int64_t ranges = range_count(n, coarse);
   char* p = static_cast<char*>(ws);
   auto take = [&](size_t bytes) { char* q = p; p += align256(bytes); return q; };
   EmbBwdWs w;
   w.skeys = (int*)take((size_t)n * 4);
   w.sort_ws = take(radix_sort_segments_workspace(n, F));
-  w.tile_counts = (int*)take((size_t)(cdiv(n, SEG_TILE) + 1) * 4);
+  w.tile_counts = (int*)take((size_t)run_words(n) * 4);
   w.range_ubefore = (int*)take((size_t)ranges * 4);
   w.part_uid = (int*)take((size_t)ranges * 4);
-  w.span_list = (int*)take((size_t)ranges * 4);
-  w.span_count = (int*)take(4);
   w.part = (float*)take((size_t)ranges * 2 * dim * 4);
   return w;
 }
@@ -903,7 +965,7 @@ static EmbBwdWs emb_bwd_ws(void* ws, int64_t nnz, int dim, int F) {
 hipError_t embbag_bwd_sort(const int64_t* row_base, int64_t max_local_rows, const int32_t* offsets,
                            const int32_t* indices, int F, int B, int64_t nnz, int dim,
                            int* unique_rows, int* seg_offsets, int* sorted_bags, int* num_unique,
-                           void* ws, hipStream_t s, void* const* ev) {
+                           void* ws, hipStream_t s, void* const* ev, bool coarse) {
   // ev (optional): 4 events, begin / end of the sort and of the run bookkeeping
   // (null entries are not recorded)
   auto record = [&](int i) -> hipError_t {
@@ -919,20 +981,22 @@ hipError_t embbag_bwd_sort(const int64_t* row_base, int64_t max_local_rows, cons
     return hipSuccess;
   }
   const int n = (int)nnz;
-  EmbBwdWs w = emb_bwd_ws(ws, nnz, dim, F);
-  hipError_t e = radix_sort_segments(indices, n, offsets, F, B, row_base, max_local_rows,
-                                     w.skeys, sorted_bags, w.sort_ws, s);
+  EmbBwdWs w = emb_bwd_ws(ws, nnz, dim, F, coarse);
+  hipError_t e = radix_sort_segments(indices, n, offsets, F, B, row_base, max_local_rows, w.skeys, sorted_bags,
+                                     w.sort_ws, s);
   if (e != hipSuccess) return e;
   LAT_HIP_CHECK(record(1));
   LAT_HIP_CHECK(record(2));
   const int tiles = cdiv(n, SEG_TILE);
-  zero_int_kernel<<<1, 64, 0, s>>>(w.span_count, 1);
-  LAT_LAUNCH_CHECK();
   seg_count_kernel<<<tiles, SEG_THREADS, 0, s>>>(w.skeys, n, w.tile_counts);
   LAT_LAUNCH_CHECK();
-  e = exclusive_scan_inplace_small(w.tile_counts, tiles, s);
-  if (e != hipSuccess) return e;
-  seg_write_kernel<<<tiles, SEG_THREADS, 0, s>>>(w.skeys, n, w.tile_counts, unique_rows,
+  // beyond 4096 tiles (16.8M lookups) a block would read too many counts
+  int* groups = tiles > 4096 ? w.tile_counts + tiles : nullptr;
+  if (groups) {
+    seg_group_kernel<<<cdiv(tiles, SEG_GROUP), SEG_THREADS, 0, s>>>(w.tile_counts, tiles, groups);
+    LAT_LAUNCH_CHECK();
+  }
+  seg_write_kernel<<<tiles, SEG_THREADS, 0, s>>>(w.skeys, n, w.tile_counts, groups, range_shift(n, coarse), unique_rows,
                                                  seg_offsets, num_unique, w.range_ubefore);
   LAT_LAUNCH_CHECK();
   LAT_HIP_CHECK(record(3));
@@ -943,7 +1007,7 @@ hipError_t embbag_bwd_apply(const int32_t* offsets, int F, int B, int64_t nnz, i
                             const void* dX, DType dxt, int n_slots, int first_slot, int dim,
                             const int* unique_rows, const int* seg_offsets, const int* sorted_bags,
                             float* grad_rows, void* E, DType et, float lr, void* ws, hipStream_t s,
-                            void* const* ev) {
+                            void* const* ev, bool coarse) {
   if (nnz == 0) {
     if (ev)
       for (int i = 0; i < 4; ++i)
@@ -956,13 +1020,13 @@ hipError_t embbag_bwd_apply(const int32_t* offsets, int F, int B, int64_t nnz, i
               (long long)B * n_slots * dim * (dxt == DT_BF16 ? 2 : 4));
     return hipErrorInvalidValue;
   }
-  EmbBwdWs w = emb_bwd_ws(ws, nnz, dim, F);
+  EmbBwdWs w = emb_bwd_ws(ws, nnz, dim, F, coarse);
   void* Eupd = lr != 0.f ? E : nullptr;
 #define LAT_RED(DTT, ETT)                                                                       \
   return embbag_bwd_reduce<DTT, ETT>(w.skeys, sorted_bags, n, dX, B, n_slots, first_slot, dim,   \
                                      offsets, mean, w.range_ubefore, w.part, w.part_uid,          \
-                                     w.span_list, w.span_count, seg_offsets, unique_rows,         \
-                                     grad_rows, Eupd, lr, s, ev)
+                                     seg_offsets, unique_rows,                                   \
+                                     grad_rows, Eupd, lr, range_shift(n, coarse), s, ev)
   if (dxt == DT_BF16 && et == DT_BF16) LAT_RED(bf16_t, bf16_t);
   if (dxt == DT_BF16 && et == DT_F32) LAT_RED(bf16_t, float);
   if (dxt == DT_F32 && et == DT_BF16) LAT_RED(float, bf16_t);
@@ -974,12 +1038,14 @@ hipError_t embbag_bwd(const int64_t* row_base, int64_t max_local_rows, const int
                       const int32_t* indices, int F, int B, int64_t nnz, int mean,
                       const void* dX, DType dxt, int n_slots, int first_slot, int dim,
                       int* unique_rows, int* seg_offsets, int* sorted_bags, int* num_unique,
-                      float* grad_rows, void* E, DType et, float lr, void* ws, hipStream_t s) {
+                      float* grad_rows, void* E, DType et, float lr, void* ws, hipStream_t s,
+                      bool coarse) {
   hipError_t e = embbag_bwd_sort(row_base, max_local_rows, offsets, indices, F, B, nnz, dim,
-                                 unique_rows, seg_offsets, sorted_bags, num_unique, ws, s, nullptr);
+                                 unique_rows, seg_offsets, sorted_bags, num_unique, ws, s, nullptr,
+                                 coarse);
   if (e != hipSuccess) return e;
   return embbag_bwd_apply(offsets, F, B, nnz, mean, dX, dxt, n_slots, first_slot, dim, unique_rows,
-                          seg_offsets, sorted_bags, grad_rows, E, et, lr, ws, s, nullptr);
+                          seg_offsets, sorted_bags, grad_rows, E, et, lr, ws, s, nullptr, coarse);
 }
 
 // ---------------------------------------------------------------------------

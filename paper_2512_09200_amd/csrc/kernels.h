@@ -6,7 +6,6 @@
 namespace lat {
 
 // sort.hip
-hipError_t exclusive_scan_inplace_small(int* a, int n, hipStream_t s);
 // Sort of a jagged batch's (global row, bag) pairs whose positions are grouped
 // by feature: each feature segment is sorted by its local row (< max_local_rows).
 // The first pass reads the batch's indices directly (keys = row_base[f] +
@@ -20,7 +19,10 @@ hipError_t radix_sort_segments(const int32_t* indices, int64_t n, const int32_t*
 hipError_t embbag_fwd(const void* E, DType edt, int dim, const int64_t* row_base,
                       const int32_t* offsets, const int32_t* indices, int F, int B, int mean,
                       void* X, DType xdt, int n_slots, int first_slot, hipStream_t s);
-size_t embbag_bwd_workspace(int64_t nnz, int dim, int F);
+// Scratch of the sparse gradient: enough for any batch of at most nnz lookups.
+// coarse: the least scratch (long reduction ranges whatever the batch); every
+// call of one gradient must say the same.
+size_t embbag_bwd_workspace(int64_t nnz, int dim, int F, bool coarse = false);
 // max_local_rows: rows of the largest table (bounds every local index).
 // The sparse gradient in two phases over one workspace: embbag_bwd_sort needs
 // only the batch -- sort, unique rows, run offsets; embbag_bwd_apply needs
@@ -30,17 +32,18 @@ size_t embbag_bwd_workspace(int64_t nnz, int dim, int F);
 hipError_t embbag_bwd_sort(const int64_t* row_base, int64_t max_local_rows, const int32_t* offsets,
                            const int32_t* indices, int F, int B, int64_t nnz, int dim,
                            int* unique_rows, int* seg_offsets, int* sorted_bags, int* num_unique,
-                           void* ws, hipStream_t s, void* const* ev);
+                           void* ws, hipStream_t s, void* const* ev, bool coarse = false);
 hipError_t embbag_bwd_apply(const int32_t* offsets, int F, int B, int64_t nnz, int mean,
                             const void* dX, DType dxt, int n_slots, int first_slot, int dim,
                             const int* unique_rows, const int* seg_offsets, const int* sorted_bags,
                             float* grad_rows, void* E, DType et, float lr, void* ws, hipStream_t s,
-                            void* const* ev);
+                            void* const* ev, bool coarse = false);
 hipError_t embbag_bwd(const int64_t* row_base, int64_t max_local_rows, const int32_t* offsets,
                       const int32_t* indices, int F, int B, int64_t nnz, int mean,
                       const void* dX, DType dxt, int n_slots, int first_slot, int dim,
                       int* unique_rows, int* seg_offsets, int* sorted_bags, int* num_unique,
-                      float* grad_rows, void* E, DType et, float lr, void* ws, hipStream_t s);
+                      float* grad_rows, void* E, DType et, float lr, void* ws, hipStream_t s,
+                      bool coarse = false);
 hipError_t validate_batch(const int64_t* row_base, const int32_t* offsets,
                           const int32_t* indices, int F, int B, int64_t nnz, int64_t max_rows,
                           unsigned long long* dev_result, hipStream_t s);

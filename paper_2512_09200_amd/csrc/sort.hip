@@ -31,14 +31,13 @@ constexpr int SORT_TILE = SORT_THREADS * SORT_ITEMS;  // 8192
 constexpr int RADIX_BITS = 8;
 constexpr int RADIX = 1 << RADIX_BITS;
 
-constexpr int SCAN_THREADS = 256;
 static_assert(SORT_THREADS >= RADIX, "one thread per digit in the scatter's tile scan");
 
 // ---------------------------------------------------------------------------
-// block-wide and small exclusive scans of int32 (counts fit int32: totals < 2^31)
+// block-wide exclusive scan of int32 (counts fit int32: totals < 2^31)
 // ---------------------------------------------------------------------------
 __device__ inline int block_exclusive_scan(int v, int* lds, int* total) {
-  // lds: at least SCAN_THREADS/64 ints
+  // lds: at least blockDim.x / 64 ints
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int x = v;
 #pragma unroll
@@ -60,48 +59,6 @@ __device__ inline int block_exclusive_scan(int v, int* lds, int* total) {
   return wbase + x - v;
 }
 
-// single block: exclusive scan of the tile sums in place (n >= 1).  Thread t
-// owns elements [t*per, (t+1)*per); they are read SCAN_REG at a time from
-// clamped positions (straight-line loads, all in flight together), and kept
-// in registers for the second sweep when per <= SCAN_REG.
-constexpr int SCAN_REG = 4;
-__global__ __launch_bounds__(1024) void scan_sums_kernel(int* __restrict__ sums, int n) {
-  __shared__ int lds[1024 / 64];
-  const int per = (n + blockDim.x - 1) / blockDim.x;
-  const int lo = threadIdx.x * per;
-  int v[SCAN_REG];
-  int s = 0;
-  for (int i0 = 0; i0 < per; i0 += SCAN_REG) {
-#pragma unroll
-    for (int r = 0; r < SCAN_REG; ++r) {
-      const int i = lo + i0 + r;
-      v[r] = sums[i < n ? i : n - 1];
-    }
-#pragma unroll
-    for (int r = 0; r < SCAN_REG; ++r)
-      if (i0 + r < per && lo + i0 + r < n) s += v[r];
-  }
-  int tot;
-  int run = block_exclusive_scan(s, lds, &tot);
-  for (int i0 = 0; i0 < per; i0 += SCAN_REG) {
-    if (per > SCAN_REG) {
-#pragma unroll
-      for (int r = 0; r < SCAN_REG; ++r) {
-        const int i = lo + i0 + r;
-        v[r] = sums[i < n ? i : n - 1];
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < SCAN_REG; ++r) {
-      const int i = lo + i0 + r;
-      if (i0 + r < per && i < n) {
-        sums[i] = run;
-        run += v[r];
-      }
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // radix sort
 // ---------------------------------------------------------------------------
@@ -121,37 +78,50 @@ static int key_bits(int64_t max_key) {
 // only as many digit passes as the largest table has row bits.  Tiles never
 // straddle segments; a pass scatters each tile inside its own segment.
 
-// tiles per segment (tile_base, scanned afterwards); also clears zero[0 .. nzero)
-__global__ __launch_bounds__(256) void seg_ntiles_kernel(const int32_t* __restrict__ offsets, int F,
-                                                         int B, int* __restrict__ tile_base,
-                                                         int* __restrict__ zero, int nzero) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < nzero) zero[i] = 0;
-  if (i <= F)
-    tile_base[i] = i < F ? (offsets[(int64_t)(i + 1) * B] - offsets[(int64_t)i * B] + SORT_TILE - 1) / SORT_TILE : 0;
+__device__ inline int seg_len(const int32_t* __restrict__ offsets, int f, int B) {
+  return offsets[(int64_t)(f + 1) * B] - offsets[(int64_t)f * B];
 }
+__device__ inline int seg_tiles(int len) { return (len + SORT_TILE - 1) / SORT_TILE; }
 
-// tile -> segment map: block f fills its segment's tiles
-__global__ __launch_bounds__(256) void seg_tilemap_kernel(const int* __restrict__ tile_base,
-                                                          int* __restrict__ tile_seg) {
-  const int f = blockIdx.x;
-  for (int t = tile_base[f] + threadIdx.x; t < tile_base[f + 1]; t += 256) tile_seg[t] = f;
-}
-
-// tile -> first bag: every non-empty bag writes its index to the tiles that
-// start inside it (each tile start lies in exactly one non-empty bag)
-__global__ __launch_bounds__(256) void seg_tilebag_kernel(const int32_t* __restrict__ offsets,
-                                                          int F, int B,
-                                                          const int* __restrict__ tile_base,
-                                                          int* __restrict__ tile_bag0) {
-  const int64_t bag = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// Everything the passes need before the digit counts, in one launch (a scan of
+// the tile counts, a tile map and two fills cost more in launches than in
+// work): a thread per bag.  A block adds up the tiles of the features before
+// its first bag's (F loads spread over the block), so no block waits for
+// another.
+//   tile_base[f]  first tile of segment f ([F]: all tiles)
+//   tile_seg[t]   segment of tile t
+//   tile_bag0[t]  first bag of tile t: every non-empty bag writes its index to
+//                 the tiles that start inside it
+//   zero          cleared
+__global__ __launch_bounds__(256) void seg_prep_kernel(const int32_t* __restrict__ offsets, int F, int B,
+                                                       int* __restrict__ tile_base, int* __restrict__ tile_seg,
+                                                       int* __restrict__ tile_bag0, int* __restrict__ zero,
+                                                       int nzero) {
+  __shared__ int red[4];
+  const int64_t bag0 = (int64_t)blockIdx.x * 256, bag = bag0 + threadIdx.x;
+  const int64_t nthreads = (int64_t)gridDim.x * 256;
+  for (int64_t i = bag; i < nzero; i += nthreads) zero[i] = 0;
+  const int f0 = (int)(bag0 / B);
+  int base = 0;
+  for (int f = threadIdx.x; f < f0; f += 256) base += seg_tiles(seg_len(offsets, f, B));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) base += __shfl_xor(base, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = base;
+  __syncthreads();
+  base = red[0] + red[1] + red[2] + red[3];
   if (bag >= (int64_t)F * B) return;
-  const int f = (int)(bag / B);
+  const int f = (int)(bag / B), b = (int)(bag - (int64_t)f * B);
+  for (int q = f0; q < f; ++q) base += seg_tiles(seg_len(offsets, q, B));
+  const int nt = seg_tiles(seg_len(offsets, f, B));
+  if (b == 0) {
+    tile_base[f] = base;
+    if (f == F - 1) tile_base[F] = base + nt;
+  }
+  for (int t = b; t < nt; t += B) tile_seg[base + t] = f;
   const int seg0 = offsets[(int64_t)f * B];
   const int lo = offsets[bag], hi = offsets[bag + 1];
   if (lo == hi) return;
-  for (int lt = (lo - seg0 + SORT_TILE - 1) / SORT_TILE; seg0 + lt * SORT_TILE < hi; ++lt)
-    tile_bag0[tile_base[f] + lt] = (int)bag;
+  for (int lt = seg_tiles(lo - seg0); seg0 + lt * SORT_TILE < hi; ++lt) tile_bag0[base + lt] = (int)bag;
 }
 
 struct SegTile {
@@ -433,15 +403,10 @@ hipError_t radix_sort_segments(const int32_t* indices, int64_t n, const int32_t*
   const int passes = bits == 0 ? 1 : (bits + RADIX_BITS - 1) / RADIX_BITS;
   const int dbits = bits == 0 ? 1 : (bits + passes - 1) / passes;
 
-  // the digit counts and tile id counters (ghist and tile_ctr are adjacent)
+  // cleared: the digit counts and tile id counters (ghist and tile_ctr are adjacent)
   const int nzero = MAX_PASSES * F * (RADIX + CTR_STRIDE);
-  seg_ntiles_kernel<<<cdiv(nzero, 256), 256, 0, s>>>(offsets, F, B, tile_base, ghist, nzero);
-  LAT_LAUNCH_CHECK();
-  hipError_t e = exclusive_scan_inplace_small(tile_base, F + 1, s);
-  if (e != hipSuccess) return e;
-  seg_tilemap_kernel<<<F, 256, 0, s>>>(tile_base, tile_seg);
-  LAT_LAUNCH_CHECK();
-  seg_tilebag_kernel<<<cdiv((int64_t)F * B, 256), 256, 0, s>>>(offsets, F, B, tile_base, tile_bag0);
+  seg_prep_kernel<<<cdiv((int64_t)F * B, 256), 256, 0, s>>>(offsets, F, B, tile_base, tile_seg, tile_bag0, ghist,
+                                                           nzero);
   LAT_LAUNCH_CHECK();
   radix_hist_all_kernel<<<tmax, SORT_THREADS, 0, s>>>(indices, offsets, row_base, F, B, tile_base,
                                                       tile_seg, passes, dbits, tmax, ghist, state);
@@ -479,13 +444,4 @@ hipError_t radix_sort_segments(const int32_t* indices, int64_t n, const int32_t*
   return hipSuccess;
 }
 
-}  // namespace lat
-
-namespace lat {
-hipError_t exclusive_scan_inplace_small(int* a, int n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  scan_sums_kernel<<<1, 1024, 0, s>>>(a, n);
-  LAT_LAUNCH_CHECK();
-  return hipSuccess;
-}
 }  // namespace lat
