@@ -27,6 +27,13 @@ SHAPES = {
     # with bias + ReLU, and the second layer's input gradient with the ReLU
     # mask; ragged M, N and K edges
     "bf16-big-tiles": ("bf16", 4000, (1032, 4040, 8), False),
+    # rows off 16-byte alignment: vectors read at any element, the last one of
+    # a row from its last 8 elements (widths of 8 k + 1 .. 8 k + 7, of 8 to 15,
+    # below 8; more than one tile; the large-tile kernel)
+    "bf16-odd-9-71-15": ("bf16", 130, (9, 71, 15), False),
+    "bf16-odd-8-13-7": ("bf16", 65, (8, 13, 7), False),
+    "bf16-odd-131-262-9": ("bf16", 300, (131, 262, 9), False),
+    "bf16-odd-big-tiles": ("bf16", 3999, (1031, 4033, 9), False),
 }
 PADDED = {"bf16-padded-in-415", "bf16-padded-in-13"}
 
