@@ -63,127 +63,6 @@ constexpr int CLD = GBN + 4;  // fp32 row stride of the staged C tile
 constexpr size_t GEMM_LDS = (size_t)2 * (GBM + GBN) * GLD * sizeof(uint16_t);  // 73,728 B
 static_assert((size_t)GBM * CLD * sizeof(float) <= GEMM_LDS, "C staging must fit the operand stages");
 
-__device__ inline void ld8f(const float* p, float* v) {
-  const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    v[i] = a[i];
-    v[4 + i] = b[i];
-  }
-}
-
-// Per-thread coefficients of the BlockNorm epilogue: a thread stores the
-// same 8 columns col.. in every row it handles, so bias, g_a, g_b (zeros
-// past N) and 1 / |group| are loaded once.
-struct NormCoef {
-  float b[8], ga[8], gb[8];
-  float inv_cnt;
-};
-
-__device__ inline void load_norm_coef(const Epi& e, int col, int N, NormCoef& c) {
-  load_gains8(e.gain, N, col, c.ga, c.gb);
-  if (e.bias && col + 8 <= N && ((uintptr_t)e.bias & 15) == 0) {
-    ld8f(e.bias + col, c.b);
-  } else {
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const bool ok = e.bias && col + t < N;
-      c.b[t] = ok ? e.bias[ok ? col + t : 0] : 0.f;
-    }
-  }
-  c.inv_cnt = inv_group_size(col, N);
-}
-
-// SwishRN with BlockNorm on 8 columns col.. of row `row` of the finished
-// fp32 tile (see the header comment).  Every lane of the wave calls it (the
-// shuffles need the whole 16-lane group); rows past M and columns past N
-// store nothing.
-template <typename CT, int GATE>
-__device__ inline void epi_blocknorm8(CT* C, int64_t ldc, int row, int col, int M, int N, float* v,
-                                      const Epi& e, const NormCoef& nc, int vec) {
-  float ss = 0.f;
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    v[t] = col + t < N ? v[t] + nc.b[t] : 0.f;
-    ss += v[t] * v[t];
-  }
-  ss = sum16(ss);
-  const float r = rsqrtf(ss * nc.inv_cnt + e.eps);
-  if (row >= M || col >= N) return;
-  if (col % NORM_TILE == 0) e.rinv[(int64_t)row * e.nblk + col / NORM_TILE] = r;
-  float o[8];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const float n = v[t] * r;
-    o[t] = (nc.ga[t] * n) * gate_fn<GATE>(nc.gb[t] * n);
-  }
-  CT* c = C + (int64_t)row * ldc + col;
-  CT* p = reinterpret_cast<CT*>(e.pre) + (int64_t)row * e.ldp + col;
-  if (vec && col + 8 <= N) {
-    if constexpr (sizeof(CT) == 2) {
-      stg16(c, Vec16<bf16_t>::pack(o));
-      stg16(p, Vec16<bf16_t>::pack(v));
-    } else {
-      stg16(c, Vec16<float>::pack(o));
-      stg16(c + 4, Vec16<float>::pack(o + 4));
-      stg16(p, Vec16<float>::pack(v));
-      stg16(p + 4, Vec16<float>::pack(v + 4));
-    }
-  } else {
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-      if (col + t < N) {
-        st(c + t, o[t]);
-        st(p + t, v[t]);
-      }
-  }
-}
-
-
-// Epilogue of 8 consecutive columns of one row with 16-byte vectors (the
-// caller guarantees alignment and col + 8 <= N).
-template <typename CT>
-__device__ inline void epi_store8(CT* C, int64_t ldc, int row, int col, float* v, const Epi& e,
-                                  int64_t bz) {
-  float t[8];
-  if (e.bias) {
-    ld8f(e.bias + col, t);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] += t[i];
-  }
-  if (e.addend) {
-    ld8f(e.addend + bz * e.s_add + (int64_t)row * e.ld_add + col, t);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] += t[i];
-  }
-  CT* c = C + (int64_t)row * ldc + col;
-  if (e.accumulate) {  // fp32 C only
-    ld8f(reinterpret_cast<const float*>(c), t);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] += t[i];
-  }
-  if (e.relu) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = v[i] > 0.f ? v[i] : 0.f;
-  }
-  if (e.mask) {
-    const int64_t mi = bz * e.s_mask + (int64_t)row * e.ldm + col;
-    if (e.mask_dt == DT_BF16) {
-      Vec16<bf16_t>::unpack(ldg16(reinterpret_cast<const bf16_t*>(e.mask) + mi), t);
-    } else {
-      ld8f(reinterpret_cast<const float*>(e.mask) + mi, t);
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = t[i] > 0.f ? v[i] : 0.f;
-  }
-  if constexpr (sizeof(CT) == 2) {
-    stg16(c, Vec16<bf16_t>::pack(v));
-  } else {
-    stg16(c, Vec16<float>::pack(v));
-    stg16(c + 4, Vec16<float>::pack(v + 4));
-  }
-}
-
 // An operand: element (r, k) of A(m,k) / B(n,k).  K-contiguous: p[r*ld + koff(k)];
 // MN-contiguous: p[koff(k)*... + r] with koff(k) counted in rows of length ld.
 // K segmentation splits k into (k / kseg, k % kseg): the segment index moves by
@@ -660,19 +539,6 @@ __device__ inline void mma_k64(const bf16_t* As, const bf16_t* Bs, int wm, int w
     __builtin_amdgcn_sched_barrier(0);
   }
 }
-
-// Grouped products (parameter untying): blockIdx.z = group.  Rows (gk = 0):
-// group z is rows off[z] .. off[z+1]-1 of A, C and the epilogue operands,
-// with its own B operand (+ z sB), bias (+ z N) and gains (+ z 2N); blocks
-// past a group's rows exit at once.  K (gk = 1): group z sums k = off[z] ..
-// off[z+1]-1 into its own C (+ z sC) and row sums (+ z M).
-constexpr int GEMM_MAX_GROUPS = 16;
-struct GroupSpec {
-  int n;    // 0: not grouped
-  int gk;
-  int off[GEMM_MAX_GROUPS + 1];
-  int64_t sB, sC;
-};
 
 // grid: x = M tiles * N tiles (renumbered per XCD), z = split index (split-K)
 // or batch index (batched) or group (grouped; never two of them).  vec:
@@ -1243,13 +1109,39 @@ static int64_t operand_span(int64_t ld, int R, int K, bool mn) {
   return mn ? ((int64_t)(K - 1) * ld + (R + 7) / 8 * 8) * 2 : ((int64_t)(R - 1) * ld + (K + 7) / 8 * 8) * 2;
 }
 // Buffer loaders: no K segmentation and both operands within 2 GiB,
-// counting the 64 k rows a last K step may address past the range (their
-// byte offsets must stay below 2^32, out of the resource's range, so that
-// they read zero rather than wrap back into it).
+// counting the k rows the last steps may address past the range (up to 256,
+// the 64 x 64 kernel's loads three steps ahead: their byte offsets must stay
+// below 2^32, out of the resource's range, so that they read zero rather than
+// wrap back into it).
 static bool gemm_use_buf(const GemmArgs& g) {
   const int64_t lim = (int64_t)1 << 31;
-  auto reach = [](int64_t ld, int R, int K, bool mn) { return operand_span(ld, R, K, mn) + (mn ? 64 * ld * 2 : 128); };
+  auto reach = [](int64_t ld, int R, int K, bool mn) { return operand_span(ld, R, K, mn) + (mn ? 320 * ld * 2 : 1024); };
   return g.kseg == 0 && reach(g.lda, g.M, g.K, g.ta) < lim && reach(g.ldb, g.N, g.K, g.tb) < lim;
+}
+
+// The 64 x 64 kernel takes single products (not batched, grouped or with the
+// BlockNorm epilogue) of which the 128 x 128 kernel would run at most 160
+// blocks, splits included: up to there it is faster (at 128 blocks 10.5 against
+// 14 us and 8.3 against 10.5; at 256 blocks of a 64-k product 10.2 against 8.0),
+// beyond, its twice as many operand bytes per FLOP cost more than the extra
+// blocks gain (512 blocks, 8192 x 1024 x 2208: 78 against 48 us).
+static bool gemm_use_small(const GemmArgs& g) {
+  return g.batch <= 1 && g.ngroups == 0 && !g.norm_gate && (!g.rowsum || g.ta) && gemm_use_buf(g) &&
+         (int64_t)cdiv(g.M, GBM) * cdiv(g.N, GBN) * gemm_splits(g) <= 160;
+}
+
+static hipError_t splitk_reduce(const GemmArgs& g, int splits, const float* ws, const float* rs_partial,
+                                hipStream_t st) {
+  const int grid = cdiv((int64_t)g.M * g.N, 256);
+  const Epi epi = make_epi(g);
+  if (g.c_dt == DT_BF16)
+    splitk_reduce_kernel<bf16_t><<<grid, 256, 0, st>>>(ws, splits, g.M, g.N, (bf16_t*)g.C, g.ldc, epi, rs_partial,
+                                                      g.rowsum);
+  else
+    splitk_reduce_kernel<float><<<grid, 256, 0, st>>>(ws, splits, g.M, g.N, (float*)g.C, g.ldc, epi, rs_partial,
+                                                     g.rowsum);
+  LAT_LAUNCH_CHECK();
+  return hipSuccess;
 }
 
 template <bool TA, bool TB, int NORM>
@@ -1285,18 +1177,27 @@ static hipError_t gemm_big_launch(const GemmArgs& g, bool aligned, hipStream_t s
 
 template <bool TA, bool TB, bool VA, bool VB, int NORM>
 static hipError_t gemm_bf16_launch(const GemmArgs& g, bool aligned, float* ws, hipStream_t st) {
+  const bool small = VA && VB && aligned && gemm_use_small(g);
   if constexpr (VA && VB) {
-    if (gemm_use_big(g)) return gemm_big_launch<TA, TB, NORM>(g, aligned, st);
+    if (!small && gemm_use_big(g)) return gemm_big_launch<TA, TB, NORM>(g, aligned, st);
   }
   constexpr bool can_buf = VA && VB;
   const bool buf = can_buf && aligned && gemm_use_buf(g);
-  const int splits = gemm_splits(g);
+  // (64 x 64 tiles already fill the chip where an input gradient would be split)
+  const int splits = small && !TA && (int64_t)cdiv(g.M, 64) * cdiv(g.N, 64) >= 128 ? 1 : gemm_splits(g);
   if (splits > 1 && !ws) {
     set_error("split-K GEMM without a workspace");
     return hipErrorInvalidValue;
   }
   int kps = (g.K + splits - 1) / splits;
   kps = ((kps + GBK - 1) / GBK) * GBK;
+  float* partial = splits > 1 ? ws : nullptr;
+  float* rs_partial = (splits > 1 && g.rowsum) ? ws + (size_t)splits * g.M * g.N : nullptr;
+  const int vec = epi_vec_ok(g);
+  if (small) {
+    hipError_t e = gemm_dma(g, DmaLaunch{splits, kps, partial, rs_partial, vec}, st);
+    return e != hipSuccess || splits == 1 ? e : splitk_reduce(g, splits, ws, rs_partial, st);
+  }
   const int batched = g.batch > 1 ? 1 : 0;
   GroupSpec grp{};
   int grid_m = g.M;
@@ -1314,9 +1215,6 @@ static hipError_t gemm_bf16_launch(const GemmArgs& g, bool aligned, float* ws, h
   Epi epi = make_epi(g);
   Opnd a{(const bf16_t*)g.A, g.lda, g.kseg, g.ksA};
   Opnd b{(const bf16_t*)g.B, g.ldb, g.kseg, g.ksB};
-  float* partial = splits > 1 ? ws : nullptr;
-  float* rs_partial = (splits > 1 && g.rowsum) ? ws + (size_t)splits * g.M * g.N : nullptr;
-  const int vec = epi_vec_ok(g);
   // The kernels use 72 KiB of dynamic LDS (above the 64 KiB default limit).
   static std::once_flag once[2][2];
   auto launch = [&](auto kern, auto* c, std::once_flag& of) {
@@ -1334,17 +1232,7 @@ static hipError_t gemm_bf16_launch(const GemmArgs& g, bool aligned, float* ws, h
     else launch(gemm_bf16_kernel<TA, TB, VA, VB, float, NORM, false>, (float*)g.C, once[1][0]);
   }
   LAT_LAUNCH_CHECK();
-  if (splits > 1) {
-    const int64_t n = (int64_t)g.M * g.N;
-    if (g.c_dt == DT_BF16)
-      splitk_reduce_kernel<bf16_t><<<cdiv(n, 256), 256, 0, st>>>(ws, splits, g.M, g.N, (bf16_t*)g.C,
-                                                                  g.ldc, epi, rs_partial, g.rowsum);
-    else
-      splitk_reduce_kernel<float><<<cdiv(n, 256), 256, 0, st>>>(ws, splits, g.M, g.N, (float*)g.C,
-                                                                 g.ldc, epi, rs_partial, g.rowsum);
-    LAT_LAUNCH_CHECK();
-  }
-  return hipSuccess;
+  return splits > 1 ? splitk_reduce(g, splits, ws, rs_partial, st) : hipSuccess;
 }
 
 template <bool TA, bool TB, int NORM = 0>

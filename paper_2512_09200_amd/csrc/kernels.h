@@ -89,6 +89,13 @@ struct GemmArgs {
 int gemm_splits(const GemmArgs& g);
 int gemm_f32_splits(const GemmArgs& g);
 hipError_t gemm_f32(const GemmArgs& g, float* ws, hipStream_t s);  // gemm_f32.hip; through gemm()
+// gemm_dma.hip (64 x 64 tiles, operands straight to LDS; through gemm())
+struct DmaLaunch {
+  int splits, kps;
+  float *partial, *rs_partial;
+  int vec;  // 16-byte epilogue vectors allowed
+};
+hipError_t gemm_dma(const GemmArgs& g, const DmaLaunch& L, hipStream_t st);
 size_t gemm_workspace(const GemmArgs& g);
 hipError_t gemm(const GemmArgs& g, void* ws, hipStream_t s);
 size_t colsum_workspace(int M, int N);

@@ -27,6 +27,10 @@ SHAPES = {
     # with bias + ReLU, and the second layer's input gradient with the ReLU
     # mask; ragged M, N and K edges
     "bf16-big-tiles": ("bf16", 4000, (1032, 4040, 8), False),
+    # more than 160 tiles of 128x128, below the large tiles: the 128x128 kernel
+    # (the smaller aligned products above take the 64x64 one), ragged edges
+    "bf16-mid-tiles": ("bf16", 2600, (456, 1032, 8), False),
+    "bf16-mid-tiles-padded": ("bf16", 2700, (451, 1028, 8), False),
     # rows off 16-byte alignment: vectors read at any element, the last one of
     # a row from its last 8 elements (widths of 8 k + 1 .. 8 k + 7, of 8 to 15,
     # below 8; more than one tile; the large-tile kernel)
@@ -35,7 +39,7 @@ SHAPES = {
     "bf16-odd-131-262-9": ("bf16", 300, (131, 262, 9), False),
     "bf16-odd-big-tiles": ("bf16", 3999, (1031, 4033, 9), False),
 }
-PADDED = {"bf16-padded-in-415", "bf16-padded-in-13"}
+PADDED = {"bf16-padded-in-415", "bf16-padded-in-13", "bf16-mid-tiles-padded"}
 
 
 def _layers(dt, dims, seed):
