@@ -19,8 +19,7 @@
 // Linear layer: Y[m, n] = act( (sum_k qa[m,k] qw[n,k]) * sa[m] * sw[n] + b[n] )
 // with the contraction on v_mfma_scale_f32_32x32x64_f8f6f4 (fp8 x fp8, unit
 // block scales: the row / tensor scales are applied in the epilogue), block
-// tile 128 x 128, K step 128 bytes, 2 x 2 waves of 64 x 64, operands staged
-// through LDS two K steps ahead as in the bf16 kernel.
+// tile 128 x 128, K step 128 bytes, 2 x 2 waves of 64 x 64, two LDS stages.
 //
 // Accumulation.  Measured on gfx950, this instruction adds its 64 products
 // and the incoming accumulator after aligning them to the largest exponent
@@ -283,62 +282,94 @@ hipError_t fp8_quantize(const void* x, DType xdt, int rows, int cols, int64_t ld
 // FP8 GEMM, C = act(A B^T * sa sw + b): A [M, K] and B [N, K] e4m3 codes with
 // row strides lda / ldb bytes (multiples of 16).
 // ---------------------------------------------------------------------------
-constexpr int F8M = 128, F8N = 128, F8K = 128, F8PAD = 16, F8LD = F8K + F8PAD;  // bytes
+// Codes go from memory straight to LDS (loads with the LDS as destination): a
+// 128-byte row of a stage is 8 units of 16 bytes, unit c of row r at c ^ ((r
+// >> 1) & 7), so that the 16 rows a fragment read serves at a time fall on
+// distinct banks; the permutation is made by the lanes' global addresses.  The
+// next K step's loads are issued after the barrier that ends the previous one
+// and waited for at the end of the current step's MFMAs, with no register or
+// LDS store between: staged through registers, the precise mode had room for
+// one register stage only and the fast mode filled all 256 registers (8192 x
+// 1024 x 2208: precise 58 -> 33 us, fast 36 -> 32 us).
+constexpr int F8M = 128, F8N = 128, F8K = 128;  // tile rows, columns, k (bytes) per step
 constexpr int F8CLD = F8N + 4;
-constexpr size_t FP8_GEMM_LDS = (size_t)2 * (F8M + F8N) * F8LD;  // 73,728 B
-static_assert((size_t)F8M * F8CLD * sizeof(float) <= FP8_GEMM_LDS, "C staging fits the operand stages");
+constexpr int F8TILE = 128 * F8K;               // bytes of an operand's stage
+constexpr size_t FP8_C_LDS = (size_t)F8M * F8CLD * sizeof(float);
+constexpr size_t FP8_GEMM_LDS = (size_t)4 * F8TILE > FP8_C_LDS ? (size_t)4 * F8TILE : FP8_C_LDS;  // 67,584 B
 
-// 128 rows x 128 bytes of one operand: 1024 16-byte vectors, 4 per thread.
-// Straight-line loads: a vector outside the matrix reads the first one
-// instead and is zeroed at the LDS store; a vector reaching past K has its
-// tail bytes zeroed.
-struct F8Tile {
-  u32x4 r[4];
-  int R_, K_, r0_, k0_;
-  bool edge_;
-  __device__ inline void load(const uint8_t* p, int64_t ld, int R, int K, int r0, int k0, bool edge) {
-    R_ = R; K_ = K; r0_ = r0; k0_ = k0; edge_ = edge;
+typedef __attribute__((address_space(3))) void f8_lds;
+typedef __attribute__((address_space(1))) void f8_glb;
+
+// An operand's loads: 4 units per thread and step (the wave's rows 32 w .. 32 w
+// + 31).  Rows past the operand repeat its last one (they feed outputs that are
+// never written); units past K read zero, except with WIDE (row strides of 2^24
+// bytes and more, loads by pointer), where they repeat the row's first unit and
+// f8_zero_tail() clears them.
+template <bool WIDE>
+struct F8Op {
+  __amdgpu_buffer_rsrc_t rs;
+  const uint8_t* p;
+  uint32_t voff[4];
+  int64_t ld;
+  int K, r0, kc[2];
+  int rmax;
+  __device__ inline void init(const uint8_t* base, int64_t ld_, int R, int K_, int r0_, int w, int lane) {
+    ld = ld_;
+    K = K_;
+    r0 = r0_;
+    rmax = R - 1 - r0;  // >= 0: the block's first row exists
+    p = base + (int64_t)r0 * ld;
+    const int64_t last = (int64_t)(rmax < F8M - 1 ? rmax : F8M - 1) * ld + (K + 15) / 16 * 16;
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p), (short)0,
+                                           (int)(uint32_t)(last < 0x7fffffff ? last : 0x7fffffff), BUF_RSRC_WORD3);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int v = threadIdx.x + i * 256;
-      const int rr = v >> 3, kc = (v & 7) * 16;
-      const int gr = r0 + rr, gk = k0 + kc;
-      const bool ok = !edge || (gr < R && gk < K);
-      r[i] = *reinterpret_cast<const u32x4*>(p + (ok ? (int64_t)gr * ld + gk : 0));
+      const int u = (w * 4 + i) * 64 + lane, r = u >> 3, c = (u & 7) ^ ((r >> 1) & 7);
+      const int rr = r < rmax ? r : rmax;
+      kc[i & 1] = c * 16;
+      voff[i] = WIDE ? (uint32_t)rr : (uint32_t)(rr * ld + c * 16);
     }
   }
-  __device__ inline void store(uint8_t* S) {
+  __device__ inline void issue(uint8_t* S, int k0, int w) const {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int v = threadIdx.x + i * 256;
-      const int rr = v >> 3, kc = (v & 7) * 16;
-      u32x4 x = r[i];
-      if (edge_) {
-        const int gr = r0_ + rr, gk = k0_ + kc;
-        if (!(gr < R_ && gk < K_)) {
-          x = u32x4{0, 0, 0, 0};
-        } else if (gk + 16 > K_) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e)
-            if (gk + e >= K_) x[e >> 2] &= ~(0xffu << (8 * (e & 3)));
-        }
+      const int k = k0 + kc[i & 1];
+      uint8_t* d = S + (w * 4 + i) * 1024;
+      if constexpr (WIDE) {
+        const uint8_t* g = p + (int64_t)voff[i] * ld + (k < K ? k : 0);
+        __builtin_amdgcn_global_load_lds((f8_glb*)g, (f8_lds*)d, 16, 0, 0);
+      } else {
+        const uint32_t o = k < K ? voff[i] + (uint32_t)k0 : 0x80000000u;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (f8_lds*)d, 16, (int)o, 0, 0, 0);
       }
-      *reinterpret_cast<u32x4*>(S + rr * F8LD + kc) = x;
     }
   }
 };
+
+// k past the range's end inside the last step (klast in 1 .. 127): zeros
+template <bool WIDE>
+__device__ inline void f8_zero_tail(uint8_t* S, int klast) {
+  if (threadIdx.x >= 128) return;
+  const int r = threadIdx.x, x = (r >> 1) & 7;
+  uint8_t* p = S + r * F8K;
+  for (int e = klast; e & 15; ++e) p[(((e >> 4) ^ x) << 4) + (e & 15)] = 0;
+  if (WIDE)
+    for (int u = (klast + 15) >> 4; u < 8; ++u) *reinterpret_cast<u32x4*>(p + ((u ^ x) << 4)) = u32x4{0, 0, 0, 0};
+}
 
 // 128 k of fp8 MFMAs on the staged tiles: each wave 2 x 2 fragments of 32 x 32;
 // a lane supplies row (lane % 32) and 32 consecutive k of each half (lane / 32).
 template <bool PRECISE>
 __device__ inline void mma_fp8_k128(const uint8_t* As, const uint8_t* Bs, int wm, int wn, int lane,
                                     f32x16 (&acc)[2][2]) {
-  const int frow = lane & 31, fk = (lane >> 5) * 32;
-  const uint8_t* as = As + (wm * 64 + frow) * F8LD + fk;
-  const uint8_t* bs = Bs + (wn * 64 + frow) * F8LD + fk;
-  auto opnd = [&](const uint8_t* p) {
-    const u32x4 lo = *reinterpret_cast<const u32x4*>(p);
-    const u32x4 hi = *reinterpret_cast<const u32x4*>(p + 16);
+  const int frow = lane & 31, x = (frow >> 1) & 7, h = (lane >> 5) * 2;
+  const uint8_t* as = As + (wm * 64 + frow) * F8K;
+  const uint8_t* bs = Bs + (wn * 64 + frow) * F8K;
+  // fragment rows 32 i + frow (the same swizzle: 32 rows apart), k half q
+  auto opnd = [&](const uint8_t* p, int i, int q) {
+    const uint8_t* r = p + i * 32 * F8K;
+    const u32x4 lo = *reinterpret_cast<const u32x4*>(r + (((4 * q + h) ^ x) << 4));
+    const u32x4 hi = *reinterpret_cast<const u32x4*>(r + (((4 * q + h + 1) ^ x) << 4));
     return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
   };
   const f32x16 zero = {};
@@ -349,16 +380,15 @@ __device__ inline void mma_fp8_k128(const uint8_t* As, const uint8_t* Bs, int wm
     i32x8 a1[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const i32x8 a0 = opnd(as + i * 32 * F8LD);
-      a1[i] = opnd(as + i * 32 * F8LD + 64);
+      const i32x8 a0 = opnd(as, i, 0);
+      a1[i] = opnd(as, i, 1);
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        c[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a0, opnd(bs + j * 32 * F8LD), zero,
-                                                                 0, 0, 0, 127, 0, 127);
+        c[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a0, opnd(bs, j, 0), zero, 0, 0, 0, 127, 0, 127);
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const i32x8 b1 = opnd(bs + j * 32 * F8LD + 64);
+      const i32x8 b1 = opnd(bs, j, 1);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
         c[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a1[i], b1, c[i][j], 0, 0, 0, 127, 0, 127);
@@ -375,10 +405,10 @@ __device__ inline void mma_fp8_k128(const uint8_t* As, const uint8_t* Bs, int wm
   for (int i = 0; i < 2; ++i) {
     // one 32-row fragment of A against both of B: the k = 0..63 and 64..127
     // halves chained through the accumulator
-    const i32x8 a0 = opnd(as + i * 32 * F8LD), a1 = opnd(as + i * 32 * F8LD + 64);
+    const i32x8 a0 = opnd(as, i, 0), a1 = opnd(as, i, 1);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const i32x8 b0 = opnd(bs + j * 32 * F8LD), b1 = opnd(bs + j * 32 * F8LD + 64);
+      const i32x8 b0 = opnd(bs, j, 0), b1 = opnd(bs, j, 1);
       // formats 0 / 0: e4m3 operands; E8M0 block scales 127 = 2^0
       f32x16 c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a0, b0, acc[i][j], 0, 0, 0, 127, 0, 127);
       acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a1, b1, c, 0, 0, 0, 127, 0, 127);
@@ -386,19 +416,13 @@ __device__ inline void mma_fp8_k128(const uint8_t* As, const uint8_t* Bs, int wm
   }
 }
 
-template <typename CT, bool RELU, bool PRECISE>
+template <typename CT, bool RELU, bool PRECISE, bool WIDE>
 __global__ __launch_bounds__(256, 2) void gemm_fp8_kernel(
     const uint8_t* __restrict__ A, int64_t lda, const float* __restrict__ sa, int sa_rowwise,
     const uint8_t* __restrict__ Bm, int64_t ldb, const float* __restrict__ sb, int sb_rowwise,
     const float* __restrict__ bias, CT* __restrict__ C, int64_t ldc, int M, int N, int K) {
   extern __shared__ __attribute__((aligned(16))) unsigned char f8_smem[];
-  uint8_t* As[2];
-  uint8_t* Bs[2];
-  As[0] = f8_smem;
-  Bs[0] = As[0] + F8M * F8LD;
-  As[1] = Bs[0] + F8N * F8LD;
-  Bs[1] = As[1] + F8M * F8LD;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = w >> 1, wn = w & 1;
   const int tiles_n = (N + F8N - 1) / F8N;
   const int tile = xcd_block(blockIdx.x, gridDim.x);
@@ -413,66 +437,33 @@ __global__ __launch_bounds__(256, 2) void gemm_fp8_kernel(
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int ktiles = (K + F8K - 1) / F8K;
-  const bool edge_m = m0 + F8M > M, edge_n = n0 + F8N > N;
-  auto load = [&](F8Tile& la, F8Tile& lb, int kt) {
-    const int k0 = kt * F8K;
-    const bool edge_k = k0 + F8K > K;
-    la.load(A, lda, M, K, m0, k0, edge_m || edge_k);
-    lb.load(Bm, ldb, N, K, n0, k0, edge_n || edge_k);
-  };
-  if constexpr (PRECISE) {
-    // One register stage (the per-block partial sums take the registers of
-    // the second): the next K step's tiles are loaded while the MFMAs consume
-    // the current LDS stage, then written to the other LDS stage.
-    F8Tile la, lb;
-    if (ktiles > 0) {
-      load(la, lb, 0);
-      la.store(As[0]);
-      lb.store(Bs[0]);
-    }
-    __syncthreads();
-    for (int kt = 0; kt < ktiles; ++kt) {
-      const int cur = kt & 1;
-      if (kt + 1 < ktiles) load(la, lb, kt + 1);
-      mma_fp8_k128<true>(As[cur], Bs[cur], wm, wn, lane, acc);
-      if (kt + 1 < ktiles) {
-        la.store(As[cur ^ 1]);
-        lb.store(Bs[cur ^ 1]);
-      }
-      __syncthreads();
-    }
-  } else {
-    // Two register stages and two LDS stages: while the MFMAs consume LDS
-    // stage s, the registers of the other stage receive the tile two K steps
-    // ahead (as in the bf16 kernel).
-    F8Tile la0, la1, lb0, lb1;
-    if (ktiles > 0) load(la0, lb0, 0);
-    if (ktiles > 1) load(la1, lb1, 1);
-    if (ktiles > 0) {
-      la0.store(As[0]);
-      lb0.store(Bs[0]);
-    }
-    __syncthreads();
-    int kt = 0;
-    for (; kt + 2 <= ktiles; kt += 2) {
-      if (kt + 2 < ktiles) load(la0, lb0, kt + 2);
-      mma_fp8_k128<false>(As[0], Bs[0], wm, wn, lane, acc);
-      la1.store(As[1]);
-      lb1.store(Bs[1]);
-      __syncthreads();
-      if (kt + 3 < ktiles) load(la1, lb1, kt + 3);
-      mma_fp8_k128<false>(As[1], Bs[1], wm, wn, lane, acc);
-      if (kt + 2 < ktiles) {
-        la0.store(As[0]);
-        lb0.store(Bs[0]);
-      }
-      __syncthreads();
-    }
-    if (kt < ktiles) {
-      mma_fp8_k128<false>(As[0], Bs[0], wm, wn, lane, acc);
-      __syncthreads();
-    }
+  F8Op<WIDE> oa, ob;
+  oa.init(A, lda, M, K, m0, w, lane);
+  ob.init(Bm, ldb, N, K, n0, w, lane);
+  if (ktiles > 0) {
+    oa.issue(f8_smem, 0, w);
+    ob.issue(f8_smem + F8TILE, 0, w);
   }
+#pragma unroll 1
+  for (int kt = 0; kt < ktiles; ++kt) {
+    // this wave's loads of the step have landed; past the barrier everybody's
+    // have, and everybody is done with the other stage
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    uint8_t* As = f8_smem + (kt & 1) * 2 * F8TILE;
+    if (kt + 1 < ktiles) {
+      uint8_t* S = f8_smem + ((kt + 1) & 1) * 2 * F8TILE;
+      oa.issue(S, (kt + 1) * F8K, w);
+      ob.issue(S + F8TILE, (kt + 1) * F8K, w);
+    } else if (K % F8K != 0 && (WIDE || K % 16 != 0)) {  // uniform
+      f8_zero_tail<WIDE>(As, K % F8K);
+      f8_zero_tail<WIDE>(As + F8TILE, K % F8K);
+      __syncthreads();
+    }
+    mma_fp8_k128<PRECISE>(As, As + F8TILE, wm, wn, lane, acc);
+  }
+  __syncthreads();
   // stage the fp32 tile, then rows of 8 columns: dequantise, bias, ReLU, store
   float* Cs = reinterpret_cast<float*>(f8_smem);
 #pragma unroll
@@ -541,19 +532,20 @@ hipError_t gemm_fp8(const uint8_t* A, int64_t lda, const float* sa, int sa_rowwi
                     DType cdt, int64_t ldc, int M, int N, int K, int relu, int fast_accum,
                     hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  static std::once_flag once;
-  std::call_once(once, [] {
-    const int lds = (int)FP8_GEMM_LDS;
-    const void* ks[] = {(const void*)gemm_fp8_kernel<bf16_t, true, true>, (const void*)gemm_fp8_kernel<bf16_t, false, true>,
-                        (const void*)gemm_fp8_kernel<float, true, true>, (const void*)gemm_fp8_kernel<float, false, true>,
-                        (const void*)gemm_fp8_kernel<bf16_t, true, false>, (const void*)gemm_fp8_kernel<bf16_t, false, false>,
-                        (const void*)gemm_fp8_kernel<float, true, false>, (const void*)gemm_fp8_kernel<float, false, false>};
-    for (const void* k : ks) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  });
   const int grid = cdiv(M, F8M) * cdiv(N, F8N);
-#define LAT_F8(CTT, RL, PR)                                                                      \
-  gemm_fp8_kernel<CTT, RL, PR><<<grid, 256, FP8_GEMM_LDS, s>>>(A, lda, sa, sa_rowwise, B, ldb, sb, \
-                                                               sb_rowwise, bias, (CTT*)C, ldc, M, N, K)
+  const bool wide = lda >= (1 << 24) || ldb >= (1 << 24);
+  auto launch = [&](auto kern, auto* c, std::once_flag& once) {
+    std::call_once(once, [&] {
+      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FP8_GEMM_LDS);
+    });
+    kern<<<grid, 256, FP8_GEMM_LDS, s>>>(A, lda, sa, sa_rowwise, B, ldb, sb, sb_rowwise, bias, c, ldc, M, N, K);
+  };
+#define LAT_F8(CTT, RL, PR)                                                                       \
+  do {                                                                                            \
+    static std::once_flag once[2];                                                                \
+    if (wide) launch(gemm_fp8_kernel<CTT, RL, PR, true>, (CTT*)C, once[1]);                       \
+    else launch(gemm_fp8_kernel<CTT, RL, PR, false>, (CTT*)C, once[0]);                           \
+  } while (0)
 #define LAT_F8P(CTT, RL) \
   do { if (fast_accum) LAT_F8(CTT, RL, false); else LAT_F8(CTT, RL, true); } while (0)
   if (cdt == DT_BF16) {

@@ -87,3 +87,27 @@ def test_fp8_linear(name, fast):
     assert np.all(diff <= bound)
     if not fast:
         assert max_rel_err(got, ref) <= 2e-2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K", [16, 72, 128, 200, 391])
+@pytest.mark.parametrize("fast", [False, True], ids=["precise", "fast"])
+def test_linear_fp8_row_strides(K, fast):
+    """Codes whose rows are 2^24 bytes apart take loads by pointer: the same
+    result, bit for bit, as from packed rows, whatever lies between the rows."""
+    from paper_2512_09200_amd import api
+    print(f"[fp8] row strides of 2^24 bytes, K={K}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(K)
+    M, N = 5, 70
+    x, w = torch.randn((M, K), device=DEV, generator=g), torch.randn((N, K), device=DEV, generator=g)
+    qa, sa = api.lattice_fp8_quantize(x)
+    qw, sw = api.lattice_fp8_quantize(w)
+    ref = api.lattice_linear_fp8_fwd(qa, sa, qw, sw, K, fast_accum=fast, out_dtype=torch.float32)
+    wide = torch.full((M, 1 << 24), 0x7f, dtype=torch.uint8, device=DEV)   # e4m3 NaN
+    wide[:, :K] = qa[:, :K]
+    got = api.lattice_linear_fp8_fwd(wide, sa, qw, sw, K, fast_accum=fast, out_dtype=torch.float32)
+    packed = torch.full(qa.shape, 0x7f, dtype=torch.uint8, device=DEV)
+    packed[:, :K] = qa[:, :K]
+    pad = api.lattice_linear_fp8_fwd(packed, sa, qw, sw, K, fast_accum=fast, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert torch.isfinite(ref).all() and torch.equal(got, ref) and torch.equal(pad, ref)
