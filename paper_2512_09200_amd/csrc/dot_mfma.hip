@@ -6,7 +6,7 @@
 // Each block of 4 waves loops over samples; a sample's X [n, d] is loaded
 // one sample ahead into registers (the next sample's loads are in flight
 // while the current one is computed).
-//   forward : X staged row-major; the tiles on or above the diagonal of
+//   forward : X staged row-major; the 32x32 tiles on or above the diagonal of
 //             X X^T are computed, the pairs i < j rounded to bf16 into a
 //             packed LDS row, which is then written out with 16-byte stores.
 //   backward: the symmetric gradient matrix S (S[i][j] = S[j][i] = g of the
@@ -14,6 +14,8 @@
 //             dX = S X is one contraction over j, with X staged transposed.
 // Accumulation is fp32; the pair values and dX are rounded to bf16 once,
 // where they are stored.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 #include "mfma_tile.h"
@@ -27,26 +29,48 @@ constexpr int DOT_MASK_WORDS = 4;  // slot bitmask words per sample (n <= 128)
 // first packed position of row i (pairs (i, i+1) .. (i, n-1))
 __device__ inline int pair_start(int i, int n) { return i * n - i * (i + 1) / 2; }
 
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // X rows: 4-byte aligned
+
+// The forward is bound by memory latency: a sample's read, products and write
+// follow one another, so what counts is how many samples a compute unit has in
+// flight.  LDS therefore holds only the n rows and the packed pairs (lanes of a
+// tile's rows past n read row n - 1; their products are not kept), and X moves
+// in 16-byte vectors: n = 97, d = 128 takes 36 KB, four blocks per compute
+// unit, where tiles padded to 128 rows took 51 KB and 4-byte loads (two blocks:
+// 100 us for 8192 samples, now 70).
 template <int NP, int D>
-__global__ __launch_bounds__(DOT_THREADS) void dot_fwd_mfma_kernel(const bf16_t* __restrict__ X,
-                                                                   int B, int n,
-                                                                   bf16_t* __restrict__ out,
-                                                                   int64_t ostride, int emit0) {
+__global__ __launch_bounds__(DOT_THREADS, 4) void dot_fwd_mfma_kernel(const bf16_t* __restrict__ X,
+                                                                      int B, int n,
+                                                                      bf16_t* __restrict__ out,
+                                                                      int64_t ostride, int emit0) {
   constexpr int LX = D + 8;
-  constexpr int TT = NP / 32;
-  constexpr int ZT = TT * (TT + 1) / 2;  // 32x32 tiles on or above the diagonal
-  constexpr int PMAX = NP * (NP - 1) / 2;
-  __shared__ __attribute__((aligned(16))) bf16_t Xs[NP * LX];
-  __shared__ __attribute__((aligned(16))) bf16_t Zp[(PMAX + 7) / 8 * 8];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int P = n * (n - 1) / 2;
+  constexpr int PER = (NP * D / 8 + DOT_THREADS - 1) / DOT_THREADS;  // vectors per thread
+  extern __shared__ __attribute__((aligned(16))) bf16_t dot_smem[];
+  bf16_t* Xs = dot_smem;            // [n][LX]
+  bf16_t* Zp = dot_smem + n * LX;   // packed pairs (n * LX * 2 is a multiple of 16)
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int P = n * (n - 1) / 2, nd = n * D;
   const int off = emit0 ? D : 0;
-  Stager<NP, D, DOT_THREADS> sx;
-  if (blockIdx.x < B) sx.load(X + (int64_t)blockIdx.x * n * D, D, n);
+  const int TT = (n + 31) / 32, ZT = TT * (TT + 1) / 2;  // tiles on or above the diagonal
+  u32x4 x[PER];
+  auto load = [&](int b) {
+    const bf16_t* g = X + (int64_t)b * nd;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+      if (q * DOT_THREADS * 8 < nd) {  // uniform
+        const int e = (threadIdx.x + q * DOT_THREADS) * 8;
+        x[q] = *reinterpret_cast<const u32x4_a4*>(g + (e < nd ? e : 0));
+      }
+  };
+  load(blockIdx.x);
   for (int b = blockIdx.x; b < B; b += gridDim.x) {
-    sx.store(Xs, LX, nullptr, 0, n);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int e = (threadIdx.x + q * DOT_THREADS) * 8;
+      if (e < nd) *reinterpret_cast<u32x4*>(Xs + (e / D) * LX + e % D) = x[q];
+    }
     __syncthreads();
-    if (b + (int)gridDim.x < B) sx.load(X + (int64_t)(b + gridDim.x) * n * D, D, n);
+    if (b + (int)gridDim.x < B) load(b + gridDim.x);
     for (int t = w; t < ZT; t += DOT_THREADS / 64) {
       int ti = 0, rem = t;
       while (rem >= TT - ti) {
@@ -54,10 +78,15 @@ __global__ __launch_bounds__(DOT_THREADS) void dot_fwd_mfma_kernel(const bf16_t*
         ++ti;
       }
       const int tj = ti + rem;
+      const int j = tj * 32 + (lane & 31), ri = ti * 32 + (lane & 31);
+      const bf16_t* pa = Xs + (ri < n ? ri : n - 1) * LX + (lane >> 5) * 8;
+      const bf16_t* pb = Xs + (j < n ? j : n - 1) * LX + (lane >> 5) * 8;
       f32x16 acc;
       zero16(acc);
-      mfma_tile<D>(acc, Xs + ti * 32 * LX, LX, Xs + tj * 32 * LX, LX);
-      const int j = tj * 32 + (lane & 31);
+#pragma unroll
+      for (int k = 0; k < D; k += 16)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(pa + k),
+                                                      *reinterpret_cast<const bf16x8*>(pb + k), acc, 0, 0, 0);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int i = ti * 32 + frag_row(r);
@@ -116,11 +145,12 @@ __global__ __launch_bounds__(DOT_THREADS, 2) void dot_bwd_mfma_kernel(
     const int m = threadIdx.x + q * DOT_THREADS;
     uint32_t v = 0;
     if (m < P) {
+      // (the quadratic's root, exact integers under it: off by at most one)
       const float c = 2.f * n - 1.f;
       int i = (int)((c - sqrtf(fmaxf(c * c - 8.f * m, 0.f))) * 0.5f);
-      i = max(0, min(i, n - 2));
-      while (i > 0 && pair_start(i, n) > m) --i;
-      while (i + 1 <= n - 2 && pair_start(i + 1, n) <= m) ++i;
+      i = i > n - 2 ? n - 2 : i;
+      i -= pair_start(i, n) > m ? 1 : 0;
+      i += i + 1 <= n - 2 && pair_start(i + 1, n) <= m ? 1 : 0;
       const int j = m - pair_start(i, n) + i + 1;
       v = (uint32_t)i | ((uint32_t)j << 8);
     }
@@ -436,6 +466,11 @@ hipError_t dot_slot_mask(const int32_t* offsets, int F, int B, int first, int ha
 
 bool dot_mfma_supported(int n, int d) { return n >= 1 && n <= 128 && (d == 64 || d == 128); }
 
+// X rows and the packed pairs in whole 16-byte vectors
+static size_t dot_fwd_lds(int n, int d) {
+  return (size_t)n * (d + 8) * 2 + ((size_t)n * (n - 1) / 2 + 7) / 8 * 16;
+}
+
 template <int NP, int D>
 static hipError_t dot_mfma_launch(bool fwd, const void* X, int B, int n, void* out,
                                   int64_t ostride, int emit0, const void* dout, int64_t dstride,
@@ -445,9 +480,13 @@ static hipError_t dot_mfma_launch(bool fwd, const void* X, int B, int n, void* o
   if (fwd && mask)
     dot_fwd_listed_kernel<NP, D><<<blocks, DOT_THREADS, 0, s>>>((const bf16_t*)X, B, n, mask,
                                                                (bf16_t*)out, ostride, emit0);
-  else if (fwd)
-    dot_fwd_mfma_kernel<NP, D><<<blocks, DOT_THREADS, 0, s>>>((const bf16_t*)X, B, n,
-                                                             (bf16_t*)out, ostride, emit0);
+  else if (fwd) {
+    // as many blocks as the LDS holds, at most 4 per compute unit (registers)
+    const size_t lds = dot_fwd_lds(n, D);
+    const int per = (int)std::min<size_t>(4, (size_t)160 * 1024 / lds);
+    dot_fwd_mfma_kernel<NP, D><<<B < 256 * per ? B : 256 * per, DOT_THREADS, lds, s>>>(
+        (const bf16_t*)X, B, n, (bf16_t*)out, ostride, emit0);
+  }
   else
     dot_bwd_mfma_kernel<NP, D><<<blocks, DOT_THREADS, 0, s>>>(
         (const bf16_t*)X, B, n, (const bf16_t*)dout, dstride, emit0, (bf16_t*)dX);
