@@ -9,12 +9,13 @@
 //   forward : X staged row-major; the 32x32 tiles on or above the diagonal of
 //             X X^T are computed, the pairs i < j rounded to bf16 into a
 //             packed LDS row, which is then written out with 16-byte stores.
-//   backward: the symmetric gradient matrix S (S[i][j] = S[j][i] = g of the
-//             pair, zero diagonal) is built in LDS from the packed gradient;
-//             dX = S X is one contraction over j, with X staged transposed.
+//   backward: dX = S X is one contraction over j, where S is the symmetric
+//             gradient matrix (S[i][j] = S[j][i] = g of the pair, zero
+//             diagonal), of which LDS holds the upper triangle.
 // Accumulation is fp32; the pair values and dX are rounded to bf16 once,
 // where they are stored.
 #include <algorithm>
+#include <mutex>
 
 #include "common.h"
 #include "kernels.h"
@@ -110,41 +111,92 @@ __global__ __launch_bounds__(DOT_THREADS, 4) void dot_fwd_mfma_kernel(const bf16
   }
 }
 
-// LDS writes of this wave visible to its own reads (wave-private patches)
-__device__ inline void dot_wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// The backward.  The symmetric gradient matrix S is kept as its strict upper
+// triangle U (U[i][j] = g of the pair i < j, zeros elsewhere), written once per
+// pair; a 32 x 16 piece of S comes from U's rows right of the diagonal, from
+// U's columns (transposed LDS reads) left of it, and from both, their bits
+// joined, on it.  X stays as it is in memory ([n][D], 16-byte vectors) and is
+// read by columns.  So X and the pairs take n rows each in LDS (50 KB at
+// n = 97, d = 128: three blocks per compute unit; with X transposed, both
+// triangles of S and a patch for the output it was 80 KB and two), and both are
+// loaded a sample ahead.  Wave w takes rows 32 ti .. of dX, its pieces of S in
+// registers, computed as dX^T = X^T S so that a lane holds neighbouring columns
+// of one row, which exchanges between lanes make 64-byte segments of dX.
+//
+// Bound by memory traffic (4.5 to 5 TB/s), short batches by latency.  8192
+// samples, d = 128: n = 97 130 -> 108 us, 65 75 -> 64, 27 37.6 -> 26.5 (96 and
+// 64, whole tiles: 97 -> 98 and 60.6 -> 59.6); d = 64, n = 27: 21.9 -> 12.9;
+// 512 samples of n = 97: 16.4 -> 12.2.
+//
+// LDS units (16 bytes) are permuted within their rows so that neither kind of
+// read has bank conflicts: 16 rows at one column, or 4 rows of 64 bytes.
+template <int D>
+__device__ inline int dot_swz_x(int k) {
+  return D == 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2;
+}
+template <int NS>
+__device__ inline int dot_swz_u(int r) {
+  const int lo = (r >> 2) & 3;
+  return NS == 128 ? ((r & 3) << 2) | lo : (NS == 64 ? (((r >> 1) & 1) << 2) | lo : lo);
+}
+
+typedef short dot_i16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) dot_i16x4 dot_lds_v4;
+
+// MFMA operand of 32 columns from c0 and 16 rows k from ks of a row-major LDS
+// matrix (lane: column lane % 32, k 8 (lane / 32) .. + 7), from the positions of its two halves.  Within each
+// 16-lane group a transposed read returns to lane j, as its element e, element
+// j % 4 of the 8-byte piece addressed by lane 4e + j / 4: a lane's pieces are
+// columns c0 + dot_frag_c(lane) .. + 3 of rows ks + dot_frag_k(lane) and + 4.
+__device__ inline int dot_frag_c(int lane) { return 16 * ((lane >> 4) & 1) + 4 * (lane & 3); }
+__device__ inline int dot_frag_k(int lane) { return 8 * (lane >> 5) + ((lane & 15) >> 2); }
+__device__ inline bf16x8 dot_frag_cols(const bf16_t* p0, const bf16_t* p4) {
+  const dot_i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dot_lds_v4*)p0);
+  const dot_i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dot_lds_v4*)p4);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// row length of U in LDS
+constexpr int dot_u_cols(int np) { return np <= 32 ? 32 : (np <= 64 ? 64 : 128); }
+// blocks per compute unit that the registers allow (and about what the LDS holds)
+constexpr int dot_bwd_blocks(int np) {
+  return np <= 80 ? 4 : (np <= 112 ? 3 : 2);
 }
 
 template <int NP, int D>
-__global__ __launch_bounds__(DOT_THREADS, 2) void dot_bwd_mfma_kernel(
+__global__ __launch_bounds__(DOT_THREADS, dot_bwd_blocks(NP)) void dot_bwd_mfma_kernel(
     const bf16_t* __restrict__ X, int B, int n, const bf16_t* __restrict__ dout, int64_t dstride,
     int emit0, bf16_t* __restrict__ dX) {
-  constexpr int LT = NP + 8, LS = NP + 8;
-  constexpr int TT = NP / 32;
+  constexpr int NS = dot_u_cols(NP);
+  constexpr int PER = (NP * D / 8 + DOT_THREADS - 1) / DOT_THREADS;  // X vectors per thread
   constexpr int PMAX = NP * (NP - 1) / 2;
-  constexpr int Q = (PMAX + DOT_THREADS - 1) / DOT_THREADS;  // pairs per thread
-  __shared__ __attribute__((aligned(16))) bf16_t XT[D * LT];
-  __shared__ __attribute__((aligned(16))) bf16_t S[NP * LS];
-  // per-wave 32 x 32 patch: dX tiles leave as 16-byte row segments
-  constexpr int LQ = 32 + 8;
-  __shared__ __attribute__((aligned(16))) bf16_t DQ[DOT_THREADS / 64][32 * LQ];
+  constexpr int Q = (PMAX + DOT_THREADS - 1) / DOT_THREADS;          // pairs per thread
+  constexpr int KS = NP / 16, AB = D / 32;
+  // n > NMIN: what is in range for every such n needs no check
+  constexpr int NMIN = NP <= 32 ? 0 : (NP <= 64 ? 32 : NP - 16);
+  constexpr int XFULL = (NMIN + 1) * D / (DOT_THREADS * 8), QFULL = (NMIN + 1) * NMIN / 2 / DOT_THREADS;
+  extern __shared__ __attribute__((aligned(16))) bf16_t dot_smem[];
+  const int nk = (n + 15) & ~15;
+  bf16_t* Xs = dot_smem;              // [nk][D], rows past n zeros
+  bf16_t* U = Xs + nk * D;            // [n][NS]
+  bf16_t* G0 = U + n * NS;            // [D] gradient of the copied row 0
   const bool vec_dx = (reinterpret_cast<uintptr_t>(dX) & 15) == 0;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int P = n * (n - 1) / 2;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int P = n * (n - 1) / 2, nd = n * D;
   const int off = emit0 ? D : 0;
-  // diagonal and padding of S stay zero; every sample rewrites all pairs
-  for (int e = threadIdx.x; e < NP * LS; e += DOT_THREADS) S[e] = 0;
-  // this thread's pairs m = tid + q * THREADS as 16-bit i | j << 8, two per
-  // register (the same for every sample): the row is the largest i with
-  // pair_start(i) <= m
-  uint32_t ijp[(Q + 1) / 2];
+  for (int e = threadIdx.x * 8; e < n * NS; e += DOT_THREADS * 8)
+    *reinterpret_cast<u32x4*>(U + e) = u32x4{0u, 0u, 0u, 0u};
+  for (int e = nd + threadIdx.x * 8; e < nk * D; e += DOT_THREADS * 8)
+    *reinterpret_cast<u32x4*>(Xs + e) = u32x4{0u, 0u, 0u, 0u};
+  // this thread's pairs m = tid + q * THREADS as positions in U, two 16-bit
+  // ones per register (the same for every sample): the row is the largest i
+  // with pair_start(i) <= m
+  uint32_t pos[(Q + 1) / 2];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int m = threadIdx.x + q * DOT_THREADS;
     uint32_t v = 0;
-    if (m < P) {
+    if (q < QFULL || m < P) {
       // (the quadratic's root, exact integers under it: off by at most one)
       const float c = 2.f * n - 1.f;
       int i = (int)((c - sqrtf(fmaxf(c * c - 8.f * m, 0.f))) * 0.5f);
@@ -152,81 +204,126 @@ __global__ __launch_bounds__(DOT_THREADS, 2) void dot_bwd_mfma_kernel(
       i -= pair_start(i, n) > m ? 1 : 0;
       i += i + 1 <= n - 2 && pair_start(i + 1, n) <= m ? 1 : 0;
       const int j = m - pair_start(i, n) + i + 1;
-      v = (uint32_t)i | ((uint32_t)j << 8);
+      v = (uint32_t)(i * NS + (((j >> 3) ^ dot_swz_u<NS>(i)) << 3) + (j & 7));
     }
-    if (q % 2 == 0) ijp[q / 2] = v;
-    else ijp[q / 2] |= v << 16;
+    if (q % 2 == 0) pos[q / 2] = v;
+    else pos[q / 2] |= v << 16;
   }
-  Stager<NP, D, DOT_THREADS> sx;
-  if (blockIdx.x < B) sx.load(X + (int64_t)blockIdx.x * n * D, D, n);
+  u32x4 x[PER];
+  uint32_t gv[Q], g0 = 0;
+  // straight-line loads (a vector or pair past the last reads the first one
+  // and is not used)
+  auto load = [&](int b) {
+    const bf16_t* gb = dout + (int64_t)b * dstride;
+    const bf16_t* xb = X + (int64_t)b * nd;
+    const bf16_t* gp = P > 0 ? gb + off : xb;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int e = (threadIdx.x + q * DOT_THREADS) * 8;
+      x[q] = *reinterpret_cast<const u32x4_a4*>(xb + (q < XFULL || e < nd ? e : 0));
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int m = threadIdx.x + q * DOT_THREADS;
+      gv[q] = gp[q < QFULL || m < P ? m : 0];
+    }
+    if (emit0) g0 = gb[threadIdx.x % D];
+  };
+  load(blockIdx.x);
   __syncthreads();
+  // rows of dX and column blocks of this wave
+  constexpr int TT = (NP + 31) / 32;
+  constexpr int WI = TT <= 1 ? 1 : (TT == 2 ? 2 : 4), WA = 4 / WI;
+  const int ti = w % WI, ab0 = w / WI;
+  const int row = ti * 32 + (lane & 31);
   for (int b = blockIdx.x; b < B; b += gridDim.x) {
-    // the pair gradients of this sample, then S and X^T into LDS
-    const bf16_t* gb = dout + (int64_t)b * dstride + off;
-    // straight-line loads (a pair past the last reads pair 0 and is not
-    // used): selecting the loaded value would make each load wait alone
-    uint32_t gv[Q];
+    const int e0 = threadIdx.x * 8, r0 = e0 / D;
+    bf16_t* xd = Xs + r0 * D + (e0 % D ^ dot_swz_x<D>(r0) << 3);  // (the same 16 rows on)
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int m = threadIdx.x + q * DOT_THREADS;
-      gv[q] = gb[m < P ? m : 0];
-    }
-    sx.store(nullptr, 0, XT, LT, n);
+    for (int q = 0; q < PER; ++q)
+      if (q < XFULL || e0 + q * DOT_THREADS * 8 < nd) *reinterpret_cast<u32x4*>(xd + q * DOT_THREADS * 8) = x[q];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int m = threadIdx.x + q * DOT_THREADS;
-      if (m < P) {
-        const uint32_t v = (ijp[q / 2] >> (16 * (q % 2))) & 0xffffu;
-        const int i = v & 0xff, j = v >> 8;
-        S[i * LS + j] = (bf16_t)gv[q];
-        S[j * LS + i] = (bf16_t)gv[q];
-      }
-    }
+    for (int q = 0; q < Q; ++q)
+      if (q < QFULL || threadIdx.x + q * DOT_THREADS < P) U[(pos[q / 2] >> (16 * (q % 2))) & 0xffffu] = (bf16_t)gv[q];
+    if (emit0 && threadIdx.x < D) G0[threadIdx.x] = (bf16_t)g0;
     __syncthreads();
-    // the slot-0 gradient of the column this wave's first tile covers, read
-    // before the next sample's loads are issued (a wait for it then does not
-    // wait for them); used only with emit0, by the tiles of row block 0
-    const bf16_t* g0 = dout + (int64_t)b * dstride;
-    const bf16_t g0raw = g0[(w % (D / 32)) * 32 + (lane & 31)];
-    if (b + (int)gridDim.x < B) sx.load(X + (int64_t)(b + gridDim.x) * n * D, D, n);
-    bf16_t* dxb = dX + (int64_t)b * n * D;
-    bf16_t* pq = DQ[w];
-    for (int t = w; t < TT * (D / 32); t += DOT_THREADS / 64) {
-      const int ti = t / (D / 32), ta = t % (D / 32);
-      f32x16 acc;
-      zero16(acc);
-      mfma_tile<NP>(acc, S + ti * 32 * LS, LS, XT + ta * 32 * LT, LT);
-      const float gz = (emit0 && ti == 0) ? bf2f(g0raw) : 0.f;  // ti == 0: t == w
-      if (vec_dx) {
-        // tile -> patch (row frag_row(r), column lane % 32) -> 16-byte row segments
+    if (b + (int)gridDim.x < B) load(b + gridDim.x);
+    if (ti * 32 < n) {  // uniform per wave
+      bf16x8 s[KS], dg[2];
+      const int fk = dot_frag_k(lane), cu = ti * 32 + dot_frag_c(lane);
+      // position of U's columns cu .. cu + 3 at row r
+      auto atu = [&](int r) { return r * NS + (((cu >> 3) ^ dot_swz_u<NS>(r)) << 3) + (cu & 7); };
+      // (the permutation is the same 16 rows on)
+      const bf16_t *u0 = U + atu(fk), *u4 = U + atu(fk + 4);
+      const int ru = row < n ? row : n - 1;
+      const bf16_t* up = U + ru * NS;
+      int fu = (dot_swz_u<NS>(ru) ^ (lane >> 5)) << 3;
+      asm volatile("" : "+v"(fu));  // the addresses are not kept in registers
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int il = frag_row(r);
-          const float v = (ti == 0 && il == 0) ? acc[r] + gz : acc[r];
-          pq[il * LQ + (lane & 31)] = f2bf(v);
+      for (int k = 0; k < KS; ++k)
+        if (k * 16 <= NMIN || k * 16 < n) {
+          if (k / 2 < ti) s[k] = dot_frag_cols(u0 + k * 16 * NS, u4 + k * 16 * NS);
+          else s[k] = *reinterpret_cast<const bf16x8*>(up + ((k * 16) ^ fu));
         }
-        dot_wave_sync();
+      // rows past the last read row n - 1, which is all zeros
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          const int rl = half * 16 + (lane >> 2), c8 = (lane & 3) * 8;
-          const int i = ti * 32 + rl;
-          if (i < n) stg16(dxb + i * D + ta * 32 + c8, *reinterpret_cast<const u32x4*>(pq + rl * LQ + c8));
-        }
-        dot_wave_sync();
-        continue;
+      for (int h = 0; h < 2; ++h) {
+        const int r = ti * 32 + h * 16 + fk;
+        dg[h] = dot_frag_cols(U + atu(r < n ? r : n - 1), U + atu(r + 4 < n ? r + 4 : n - 1));
       }
-      const int a = ta * 32 + (lane & 31);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = ti * 32 + frag_row(r);
-        if (i < n) {
-          float v = acc[r];
-          if (i == 0) v += gz;
-          dxb[i * D + a] = f2bf(v);
+      for (int k = 0; k < KS; ++k)
+        if (k / 2 == ti)
+          s[k] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, s[k]) | __builtin_bit_cast(u32x4, dg[k & 1]));
+      bf16_t* dxr = dX + ((int64_t)b * n + ti * 32 + (lane & 15)) * D + ((lane >> 4) & 1) * 16 + (lane >> 5) * 8;
+#pragma unroll 1
+      for (int ab = ab0; ab < AB; ab += WA) {
+        f32x16 acc;
+        zero16(acc);
+        const int cx = ab * 32 + dot_frag_c(lane);
+        const bf16_t* px = Xs + fk * D + (cx ^ dot_swz_x<D>(fk) << 3);  // (the same 4 rows on)
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+          if (k * 16 <= NMIN || k * 16 < n) {
+            const bf16x8 xf = dot_frag_cols(px + k * 16 * D, px + (k * 16 + 4) * D);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, s[k], acc, 0, 0, 0);
+          }
+        if (emit0 && ti == 0 && lane % 32 == 0) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[r] += bf2f(G0[ab * 32 + frag_row(r)]);
+        }
+        // registers 4q .. 4q + 3: columns 8q + 4 (lane / 32) .. + 3
+        uint32_t p[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) p[q] = (uint32_t)f2bf(acc[2 * q]) | (uint32_t)f2bf(acc[2 * q + 1]) << 16;
+        // Half waves exchange, so that a lane has 8 columns (those from 16 h + 8
+        // (lane / 32)), then 16-lane groups, so that four lanes have a row's 32
+        // (rows lane % 16 and 16 on): 64-byte row segments.
+        u32x4 v[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const auto lo = __builtin_amdgcn_permlane32_swap(p[4 * h], p[4 * h + 2], false, false);
+          const auto hi = __builtin_amdgcn_permlane32_swap(p[4 * h + 1], p[4 * h + 3], false, false);
+          v[h] = u32x4{lo[0], hi[0], lo[1], hi[1]};
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const auto t = __builtin_amdgcn_permlane16_swap(v[0][e], v[1][e], false, false);
+          v[0][e] = t[0];
+          v[1][e] = t[1];
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if (ti * 32 + h * 16 + (lane & 15) >= n) continue;
+          bf16_t* d = dxr + h * 16 * D + ab * 32;
+          if (vec_dx) stg16(d, v[h]);
+          else
+#pragma unroll
+            for (int e = 0; e < 8; ++e) d[e] = (bf16_t)(v[h][e / 2] >> (16 * (e % 2)));
         }
       }
     }
-    __syncthreads();  // S and XT are rewritten for the next sample
+    __syncthreads();  // Xs, U and G0 are rewritten for the next sample
   }
 }
 
@@ -471,25 +568,41 @@ static size_t dot_fwd_lds(int n, int d) {
   return (size_t)n * (d + 8) * 2 + ((size_t)n * (n - 1) / 2 + 7) / 8 * 16;
 }
 
+static size_t dot_bwd_lds(int n, int np, int d) { return ((size_t)((n + 15) / 16 * 16 + 1) * d + (size_t)n * dot_u_cols(np)) * 2; }
+
 template <int NP, int D>
-static hipError_t dot_mfma_launch(bool fwd, const void* X, int B, int n, void* out,
-                                  int64_t ostride, int emit0, const void* dout, int64_t dstride,
-                                  void* dX, const uint32_t* mask, hipStream_t s) {
-  if (B == 0) return hipSuccess;
-  const int blocks = B < DOT_BLOCKS ? B : DOT_BLOCKS;
-  if (fwd && mask)
+static hipError_t dot_bwd_launch(const void* X, int B, int n, const void* dout, int64_t dstride, int emit0, void* dX,
+                                 hipStream_t s) {
+  auto kern = dot_bwd_mfma_kernel<NP, D>;
+  const size_t lds = dot_bwd_lds(n, NP, D);
+  static std::once_flag once;
+  static hipError_t attr = hipSuccess;
+  std::call_once(once, [&] {
+    attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)dot_bwd_lds(NP, NP, D));
+  });
+  LAT_HIP_CHECK(attr);
+  const int per = (int)std::min<size_t>(dot_bwd_blocks(NP), (size_t)160 * 1024 / lds);
+  kern<<<B < 256 * per ? B : 256 * per, DOT_THREADS, lds, s>>>((const bf16_t*)X, B, n, (const bf16_t*)dout, dstride,
+                                                               emit0, (bf16_t*)dX);
+  LAT_LAUNCH_CHECK();
+  return hipSuccess;
+}
+
+template <int NP, int D>
+static hipError_t dot_fwd_launch(const void* X, int B, int n, void* out, int64_t ostride, int emit0,
+                                 const uint32_t* mask, hipStream_t s) {
+  if (mask) {
+    const int blocks = B < DOT_BLOCKS ? B : DOT_BLOCKS;
     dot_fwd_listed_kernel<NP, D><<<blocks, DOT_THREADS, 0, s>>>((const bf16_t*)X, B, n, mask,
                                                                (bf16_t*)out, ostride, emit0);
-  else if (fwd) {
+  } else {
     // as many blocks as the LDS holds, at most 4 per compute unit (registers)
     const size_t lds = dot_fwd_lds(n, D);
     const int per = (int)std::min<size_t>(4, (size_t)160 * 1024 / lds);
     dot_fwd_mfma_kernel<NP, D><<<B < 256 * per ? B : 256 * per, DOT_THREADS, lds, s>>>(
         (const bf16_t*)X, B, n, (bf16_t*)out, ostride, emit0);
   }
-  else
-    dot_bwd_mfma_kernel<NP, D><<<blocks, DOT_THREADS, 0, s>>>(
-        (const bf16_t*)X, B, n, (const bf16_t*)dout, dstride, emit0, (bf16_t*)dX);
   LAT_LAUNCH_CHECK();
   return hipSuccess;
 }
@@ -497,11 +610,16 @@ static hipError_t dot_mfma_launch(bool fwd, const void* X, int B, int n, void* o
 hipError_t dot_mfma(bool fwd, const void* X, int B, int n, int d, void* out, int64_t ostride,
                     int emit0, const void* dout, int64_t dstride, void* dX, const uint32_t* mask,
                     hipStream_t s) {
+  if (B == 0 && dot_mfma_supported(n, d)) return hipSuccess;
 #define LAT_DOTM(NPV, DV)                                                                  \
-  if (n <= NPV && d == DV)                                                                 \
-    return dot_mfma_launch<NPV, DV>(fwd, X, B, n, out, ostride, emit0, dout, dstride, dX, mask, s);
+  if (fwd && n <= NPV && d == DV) return dot_fwd_launch<NPV, DV>(X, B, n, out, ostride, emit0, mask, s);
   LAT_DOTM(32, 64) LAT_DOTM(64, 64) LAT_DOTM(96, 64) LAT_DOTM(128, 64)
   LAT_DOTM(32, 128) LAT_DOTM(64, 128) LAT_DOTM(96, 128) LAT_DOTM(128, 128)
+#undef LAT_DOTM
+#define LAT_DOTM(NPV, DV)                                                                  \
+  if (!fwd && n <= NPV && d == DV) return dot_bwd_launch<NPV, DV>(X, B, n, dout, dstride, emit0, dX, s);
+  LAT_DOTM(32, 64) LAT_DOTM(64, 64) LAT_DOTM(80, 64) LAT_DOTM(96, 64) LAT_DOTM(112, 64) LAT_DOTM(128, 64)
+  LAT_DOTM(32, 128) LAT_DOTM(64, 128) LAT_DOTM(80, 128) LAT_DOTM(96, 128) LAT_DOTM(112, 128) LAT_DOTM(128, 128)
 #undef LAT_DOTM
   set_error("DOT MFMA path: unsupported shape n=%d d=%d", n, d);
   return hipErrorInvalidValue;

@@ -55,6 +55,19 @@ CASES = {
     "dot-f32-n128-d64": ("dot", "f32", 20, 128, 64, 0, False, False),
     "dot-bf16-n27-d32": ("dot", "bf16", 66, 27, 32, 0, True, False),
     "dot-bf16-n40-d256": ("dot", "bf16", 30, 40, 256, 0, True, False),
+    # bf16 DOT backward: first and last n of each tile count, contraction edges
+    # (multiples of 16), more samples than resident blocks
+    "dot-bf16-n16-d128": ("dot", "bf16", 25, 16, 128, 0, True, False),
+    "dot-bf16-n17-d64": ("dot", "bf16", 25, 17, 64, 0, False, False),
+    "dot-bf16-n49-d64-many": ("dot", "bf16", 1100, 49, 64, 0, True, False),
+    "dot-bf16-n65-d128-many": ("dot", "bf16", 800, 65, 128, 0, False, False),
+    "dot-bf16-n80-d64": ("dot", "bf16", 30, 80, 64, 0, True, False),
+    "dot-bf16-n81-d64": ("dot", "bf16", 30, 81, 64, 0, False, False),
+    "dot-bf16-n96-d128": ("dot", "bf16", 30, 96, 128, 0, True, False),
+    "dot-bf16-n97-d64": ("dot", "bf16", 30, 97, 64, 0, True, False),
+    "dot-bf16-n112-d128-many": ("dot", "bf16", 600, 112, 128, 0, True, False),
+    "dot-bf16-n113-d128": ("dot", "bf16", 30, 113, 128, 0, False, False),
+    "dot-bf16-n128-d128": ("dot", "bf16", 30, 128, 128, 0, True, False),
     # outside every MFMA path (d not a multiple of 16, rank over 64)
     "dot-f32-n9-d24": ("dot", "f32", 20, 9, 24, 0, True, False),
     "fm-f32-n12-d32-k70": ("fm", "f32", 20, 12, 32, 70, True, False),
