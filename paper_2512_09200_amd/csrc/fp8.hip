@@ -446,9 +446,9 @@ __global__ __launch_bounds__(256, 2) void gemm_fp8_kernel(
   }
 #pragma unroll 1
   for (int kt = 0; kt < ktiles; ++kt) {
-    // this wave's loads of the step have landed; past the barrier everybody's
-    // have, and everybody is done with the other stage
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // this wave's loads of the step have landed and its LDS reads of the other
+    // stage returned; past the barrier everybody's have, so that stage is free
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     uint8_t* As = f8_smem + (kt & 1) * 2 * F8TILE;
