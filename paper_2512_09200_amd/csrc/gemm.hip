@@ -1120,14 +1120,24 @@ static bool gemm_use_buf(const GemmArgs& g) {
 }
 
 // The 64 x 64 kernel takes single products (not batched, grouped or with the
-// BlockNorm epilogue) of which the 128 x 128 kernel would run at most 160
-// blocks, splits included: up to there it is faster (at 128 blocks 10.5 against
-// 14 us and 8.3 against 10.5; at 256 blocks of a 64-k product 10.2 against 8.0),
-// beyond, its twice as many operand bytes per FLOP cost more than the extra
-// blocks gain (512 blocks, 8192 x 1024 x 2208: 78 against 48 us).
-static bool gemm_use_small(const GemmArgs& g) {
-  return g.batch <= 1 && g.ngroups == 0 && !g.norm_gate && (!g.rowsum || g.ta) && gemm_use_buf(g) &&
-         (int64_t)cdiv(g.M, GBM) * cdiv(g.N, GBN) * gemm_splits(g) <= 160;
+// BlockNorm epilogue) of which the 128 x 128 kernel would run few blocks, splits
+// included.  Rows aligned to 16 bytes: at most 160; up to there it is faster (at
+// 128 blocks 10.5 against 14 us and 8.3 against 10.5; at 256 blocks of a 64-k
+// product 10.2 against 8.0), beyond, its twice as many operand bytes per FLOP
+// cost more than the extra blocks gain (512 blocks, 8192 x 1024 x 2208: 78
+// against 48 us).  Other rows, where the 128 x 128 kernel has to load by pointer:
+// as long as that kernel leaves compute units without a block (below 256), and
+// to 384 blocks where K is short enough for the start and end of a block to
+// count.  MLP of k_in -> 512 -> 8 with odd k_in, forward and backward, with the
+// 128 x 128 kernel and this one: 128 x 3071 99 -> 63 us, 2048 x 415 85 -> 60,
+// 2048 x 1231 104 -> 78, 4096 x 3071 (first product 128 blocks) 177 -> 157;
+// 256 blocks: 8192 x 415 106 -> 95, 8192 x 1231 160 -> 158, but 8192 x 3071
+// 226 -> 233; 320 blocks of K = 1024 151 -> 145; 512 and more, K over 1024:
+// 210 -> 217.
+static bool gemm_use_small(const GemmArgs& g, bool aligned) {
+  if (g.batch > 1 || g.ngroups > 0 || g.norm_gate || (g.rowsum && !g.ta) || !gemm_use_buf(g)) return false;
+  const int64_t blocks = (int64_t)cdiv(g.M, GBM) * cdiv(g.N, GBN) * gemm_splits(g);
+  return aligned ? blocks <= 160 : blocks < 256 || (blocks <= 384 && g.K <= 1024);
 }
 
 static hipError_t splitk_reduce(const GemmArgs& g, int splits, const float* ws, const float* rs_partial,
@@ -1175,9 +1185,10 @@ static hipError_t gemm_big_launch(const GemmArgs& g, bool aligned, hipStream_t s
   return hipSuccess;
 }
 
+// aligned: rows of both operands on 16 bytes; any: both may start on any element
 template <bool TA, bool TB, bool VA, bool VB, int NORM>
-static hipError_t gemm_bf16_launch(const GemmArgs& g, bool aligned, float* ws, hipStream_t st) {
-  const bool small = VA && VB && aligned && gemm_use_small(g);
+static hipError_t gemm_bf16_launch(const GemmArgs& g, bool aligned, bool any, float* ws, hipStream_t st) {
+  const bool small = VA && VB && (aligned || any) && gemm_use_small(g, aligned);
   if constexpr (VA && VB) {
     if (!small && gemm_use_big(g)) return gemm_big_launch<TA, TB, NORM>(g, aligned, st);
   }
@@ -1195,7 +1206,7 @@ static hipError_t gemm_bf16_launch(const GemmArgs& g, bool aligned, float* ws, h
   float* rs_partial = (splits > 1 && g.rowsum) ? ws + (size_t)splits * g.M * g.N : nullptr;
   const int vec = epi_vec_ok(g);
   if (small) {
-    hipError_t e = gemm_dma(g, DmaLaunch{splits, kps, partial, rs_partial, vec}, st);
+    hipError_t e = gemm_dma(g, DmaLaunch{splits, kps, partial, rs_partial, vec, !aligned}, st);
     return e != hipSuccess || splits == 1 ? e : splitk_reduce(g, splits, ws, rs_partial, st);
   }
   const int batched = g.batch > 1 ? 1 : 0;
@@ -1259,10 +1270,10 @@ static hipError_t gemm_bf16_dispatch(const GemmArgs& g, float* ws, hipStream_t s
   const bool ua = g.kseg == 0 && (TA ? g.M : g.K) >= 8 && !(TA && g.ngroups > 0 && !g.gk);
   const bool ub = g.kseg == 0 && (TB ? g.N : g.K) >= 8;
   const bool aligned = va && vb;
-  if ((va || ua) && (vb || ub)) return gemm_bf16_launch<TA, TB, true, true, NORM>(g, aligned, ws, st);
-  if (va || ua) return gemm_bf16_launch<TA, TB, true, false, NORM>(g, false, ws, st);
-  if (vb || ub) return gemm_bf16_launch<TA, TB, false, true, NORM>(g, false, ws, st);
-  return gemm_bf16_launch<TA, TB, false, false, NORM>(g, false, ws, st);
+  if ((va || ua) && (vb || ub)) return gemm_bf16_launch<TA, TB, true, true, NORM>(g, aligned, ua && ub, ws, st);
+  if (va || ua) return gemm_bf16_launch<TA, TB, true, false, NORM>(g, false, false, ws, st);
+  if (vb || ub) return gemm_bf16_launch<TA, TB, false, true, NORM>(g, false, false, ws, st);
+  return gemm_bf16_launch<TA, TB, false, false, NORM>(g, false, false, ws, st);
 }
 
 hipError_t gemm(const GemmArgs& g0, void* ws, hipStream_t st) {

@@ -1,6 +1,6 @@
 // bf16 contractions of few tiles: C[m, n] = epilogue( sum_k A(m, k) B(n, k) ),
-// each operand K-contiguous or M-contiguous, rows aligned to 16 bytes and
-// operands below 2 GiB.  gemm() takes this kernel for products that would
+// each operand K-contiguous or M-contiguous, rows aligned to 16 bytes (or, with
+// REG, on any element) and operands below 2 GiB.  gemm() takes this kernel for products that would
 // leave most of the chip without a 128 x 128 tile (gemm_use_small); such a
 // product is bound by the chain of K steps a block walks and by a launch's
 // start and end, not by the matrix cores.
@@ -41,7 +41,7 @@ constexpr int D_THREADS = 512, D_STAGES = 4;
 constexpr int D_TILE = DT * DK;                    // elements of an operand's stage
 constexpr int CLD = DT + 4;                        // row stride of the staged fp32 tile
 constexpr size_t DMA_LDS = (size_t)D_STAGES * 2 * D_TILE * 2;  // 65,536 B: two blocks per compute unit
-static_assert((size_t)DT * CLD * 4 <= DMA_LDS, "C staging fits the operand stages");
+static_assert((size_t)DT * CLD * 4 <= DMA_LDS / 2, "C staging fits the operand stages");
 static_assert(D_TILE / 8 == D_THREADS, "one 16-byte unit per thread, operand and step");
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -98,6 +98,56 @@ __device__ inline void zero_tail(bf16_t* S, int klast) {
   }
 }
 
+// Operands whose rows start on any element (odd widths), whose units the LDS
+// loads cannot take: the same units of the same layout through registers, by
+// 16-byte loads from any address, two steps ahead.  A unit that reaches past a
+// row's end is read from the row's last 8 elements and shifted into place at
+// the LDS store (its length is at least 8); what lies past kend becomes zeros
+// (kend is K or a multiple of 64); rows past R feed outputs that are never
+// written.  An MLP of 415 -> 512 -> 8 over 2048 samples, forward and backward,
+// whose W rows are such: 85 us with 128 x 128 tiles, 60 with these.
+typedef uint32_t d_u32x4 __attribute__((ext_vector_type(4), aligned(2)));
+template <bool MN>
+struct RegOp {
+  const bf16_t* p;  // MN: the unit at k = 0; K-contiguous: its row
+  int64_t ld;
+  u32x4 x[2];
+  int kc, sh, K, kend;
+  __device__ inline void init(const bf16_t* base, int64_t ld_, int R, int K_, int kend_, int r0) {
+    ld = ld_;
+    K = K_;
+    kend = kend_;
+    const int u = threadIdx.x, q = u >> 3;
+    if (MN) {
+      const int r = r0 + (((u & 7) ^ dma_swz_mn(q)) << 3);
+      const int rr = r >= R ? 0 : (r + 8 > R ? R - 8 : r);
+      sh = r >= R ? 0 : r - rr;
+      kc = q;
+      p = base + rr;
+    } else {
+      kc = ((u & 7) ^ ((q >> 1) & 7)) << 3;
+      sh = 0;
+      p = base + (int64_t)(r0 + q < R ? r0 + q : R - 1) * ld;
+    }
+  }
+  __device__ inline int at(int k) const { return k + 8 > K ? K - 8 : k; }
+  // a step past the range reads valid elements (k = 0) and is not used
+  template <int SLOT>
+  __device__ inline void load(int k0) {
+    const int k = k0 + kc;
+    const bf16_t* g = MN ? p + (k < kend ? (int64_t)k * ld : 0) : p + (k < kend ? at(k) : 0);
+    x[SLOT] = *reinterpret_cast<const d_u32x4*>(g);
+  }
+  template <int SLOT>
+  __device__ inline void store(bf16_t* S, int k0) const {
+    const int k = k0 + kc;
+    const int n = MN ? sh : (k < kend ? k - at(k) : 0);
+    u32x4 v = __builtin_bit_cast(u32x4, __builtin_bit_cast(unsigned __int128, x[SLOT]) >> (16 * n));
+    if (k >= kend) v = u32x4{0u, 0u, 0u, 0u};
+    *reinterpret_cast<u32x4*>(S + threadIdx.x * 8) = v;
+  }
+};
+
 // MFMA operand fragment: 32 rows from rbase, 16 k from ks (lane: row lane % 32,
 // k 8 (lane / 32) .. + 7)
 template <bool MN>
@@ -124,7 +174,7 @@ __device__ inline bf16x8 dma_frag(const bf16_t* S, int rbase, int ks, int lane) 
 // grid: x = M tiles * N tiles (renumbered per XCD), z = split.  rowsum (TA
 // only): rowsum[m] = sum over k of A(m, k), by the blocks of the first N tile;
 // with split-K each split's sum goes to rs_partial[split][m].
-template <bool TA, bool TB, typename CT>
+template <bool TA, bool TB, typename CT, bool REG>
 __global__ __launch_bounds__(D_THREADS, 4) void gemm_dma_kernel(
     const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ Bm, int64_t ldb, CT* __restrict__ C,
     int64_t ldc, int M, int N, int K, int k_per_split, float* __restrict__ partial, Epi epi, int vec,
@@ -142,41 +192,14 @@ __global__ __launch_bounds__(D_THREADS, 4) void gemm_dma_kernel(
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 
-  DmaOp<TA> oa;
-  DmaOp<TB> ob;
-  oa.init(A, lda, M, kbeg, kend, m0);
-  ob.init(Bm, ldb, N, kbeg, kend, n0);
   const int steps = kend > kbeg ? (kend - kbeg + DK - 1) / DK : 0;
-  auto issue = [&](int t) {
-    bf16_t* S = smem + (t & (D_STAGES - 1)) * 2 * D_TILE;
-    oa.issue(S, kbeg + t * DK, w);
-    ob.issue(S + D_TILE, kbeg + t * DK, w);
-  };
   // row sums of an M-contiguous A: thread = 8 rows of one k of the step
   const bool rs_on = TA && rowsum != nullptr && n0 == 0;
   float rs[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) rs[e] = 0.f;
-#pragma unroll
-  for (int t = 0; t < D_STAGES - 1; ++t) issue(t);
-#pragma unroll 1
-  for (int t = 0; t < steps; ++t) {
-    // this wave's two loads of step t have landed (those of the two steps
-    // after it may be in flight); past the barrier everybody's have, and
-    // everybody is done with step t - 1, whose stage the new loads overwrite
-    static_assert(D_STAGES == 4, "the count below");
-    asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    bf16_t* As = smem + (t & (D_STAGES - 1)) * 2 * D_TILE;
-    bf16_t* Bs = As + D_TILE;
-    if ((!TA || !TB) && t == steps - 1 && ((kend - kbeg) & 7) != 0) {  // uniform
-      const int klast = kend - kbeg - t * DK;
-      if (!TA) zero_tail(As, klast);
-      if (!TB) zero_tail(Bs, klast);
-      __syncthreads();
-    }
-    issue(t + D_STAGES - 1);
+  auto mma = [&](const bf16_t* As) {
+    const bf16_t* Bs = As + D_TILE;
 #pragma unroll
     for (int k = 0; k < DK / 2; k += 16) {
       const int ks = kg * (DK / 2) + k;
@@ -193,11 +216,78 @@ __global__ __launch_bounds__(D_THREADS, 4) void gemm_dma_kernel(
         for (int e = 0; e < 8; ++e) rs[e] += v[e];
       }
     }
+  };
+  if constexpr (REG) {
+    // step t in LDS stage t % 2 and, before that, register slot t % 2
+    RegOp<TA> oa;
+    RegOp<TB> ob;
+    oa.init(A, lda, M, K, kend, m0);
+    ob.init(Bm, ldb, N, K, kend, n0);
+    bf16_t* S1 = smem + 2 * D_TILE;
+    if (steps > 0) {
+      oa.template load<0>(kbeg);
+      ob.template load<0>(kbeg);
+      oa.template load<1>(kbeg + DK);
+      ob.template load<1>(kbeg + DK);
+      oa.template store<0>(smem, kbeg);
+      ob.template store<0>(smem + D_TILE, kbeg);
+      oa.template load<0>(kbeg + 2 * DK);
+      ob.template load<0>(kbeg + 2 * DK);
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int t = 0; t < steps; t += 2) {
+      const int k0 = kbeg + t * DK;
+      mma(smem);
+      oa.template store<1>(S1, k0 + DK);
+      ob.template store<1>(S1 + D_TILE, k0 + DK);
+      oa.template load<1>(k0 + 3 * DK);
+      ob.template load<1>(k0 + 3 * DK);
+      __syncthreads();
+      if (t + 1 == steps) break;  // uniform
+      mma(S1);
+      oa.template store<0>(smem, k0 + 2 * DK);
+      ob.template store<0>(smem + D_TILE, k0 + 2 * DK);
+      oa.template load<0>(k0 + 4 * DK);
+      ob.template load<0>(k0 + 4 * DK);
+      __syncthreads();
+    }
+  } else {
+    DmaOp<TA> oa;
+    DmaOp<TB> ob;
+    oa.init(A, lda, M, kbeg, kend, m0);
+    ob.init(Bm, ldb, N, kbeg, kend, n0);
+    auto issue = [&](int t) {
+      bf16_t* S = smem + (t & (D_STAGES - 1)) * 2 * D_TILE;
+      oa.issue(S, kbeg + t * DK, w);
+      ob.issue(S + D_TILE, kbeg + t * DK, w);
+    };
+#pragma unroll
+    for (int t = 0; t < D_STAGES - 1; ++t) issue(t);
+#pragma unroll 1
+    for (int t = 0; t < steps; ++t) {
+      // this wave's two loads of step t have landed (those of the two steps
+      // after it may be in flight) and its LDS reads of step t - 1 returned; past
+      // the barrier everybody's have, so the new loads may overwrite that stage
+      static_assert(D_STAGES == 4, "the count below");
+      asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      bf16_t* As = smem + (t & (D_STAGES - 1)) * 2 * D_TILE;
+      if ((!TA || !TB) && t == steps - 1 && ((kend - kbeg) & 7) != 0) {  // uniform
+        const int klast = kend - kbeg - t * DK;
+        if (!TA) zero_tail(As, klast);
+        if (!TB) zero_tail(As + D_TILE, klast);
+        __syncthreads();
+      }
+      issue(t + D_STAGES - 1);
+      mma(As);
+    }
+    // the loads issued past the last step write LDS: none may be in flight when
+    // the epilogue reuses it
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
   }
-  // the loads issued past the last step write LDS: none may be in flight when
-  // the epilogue reuses it
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
   float* Cs = reinterpret_cast<float*>(gemm_smem);
   if constexpr (TA) {
     if (rs_on) {
@@ -252,32 +342,34 @@ __global__ __launch_bounds__(D_THREADS, 4) void gemm_dma_kernel(
   }
 }
 
-template <bool TA, bool TB, typename CT>
+template <bool TA, bool TB, typename CT, bool REG>
 static hipError_t dma_launch(const GemmArgs& g, const DmaLaunch& L, hipStream_t st) {
-  auto kern = gemm_dma_kernel<TA, TB, CT>;
+  auto kern = gemm_dma_kernel<TA, TB, CT, REG>;
+  constexpr size_t lds = REG ? DMA_LDS / 2 : DMA_LDS;  // two stages, four
   static std::once_flag once;
   static hipError_t attr = hipSuccess;
   std::call_once(once, [&] {
-    attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)DMA_LDS);
+    attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   });
   LAT_HIP_CHECK(attr);
   const dim3 grid((unsigned)((int64_t)cdiv(g.N, DT) * cdiv(g.M, DT)), 1, L.splits);
-  kern<<<grid, D_THREADS, DMA_LDS, st>>>((const bf16_t*)g.A, g.lda, (const bf16_t*)g.B, g.ldb, (CT*)g.C, g.ldc, g.M,
+  kern<<<grid, D_THREADS, lds, st>>>((const bf16_t*)g.A, g.lda, (const bf16_t*)g.B, g.ldb, (CT*)g.C, g.ldc, g.M,
                                          g.N, g.K, L.kps, L.partial, make_epi(g), L.vec, g.rowsum, L.rs_partial);
   LAT_LAUNCH_CHECK();
   return hipSuccess;
 }
 
-template <typename CT>
+template <typename CT, bool REG>
 static hipError_t dma_ct(const GemmArgs& g, const DmaLaunch& L, hipStream_t st) {
-  if (!g.ta && !g.tb) return dma_launch<false, false, CT>(g, L, st);
-  if (!g.ta) return dma_launch<false, true, CT>(g, L, st);
-  if (!g.tb) return dma_launch<true, false, CT>(g, L, st);
-  return dma_launch<true, true, CT>(g, L, st);
+  if (!g.ta && !g.tb) return dma_launch<false, false, CT, REG>(g, L, st);
+  if (!g.ta) return dma_launch<false, true, CT, REG>(g, L, st);
+  if (!g.tb) return dma_launch<true, false, CT, REG>(g, L, st);
+  return dma_launch<true, true, CT, REG>(g, L, st);
 }
 
 hipError_t gemm_dma(const GemmArgs& g, const DmaLaunch& L, hipStream_t st) {
-  return g.c_dt == DT_BF16 ? dma_ct<bf16_t>(g, L, st) : dma_ct<float>(g, L, st);
+  if (L.reg) return g.c_dt == DT_BF16 ? dma_ct<bf16_t, true>(g, L, st) : dma_ct<float, true>(g, L, st);
+  return g.c_dt == DT_BF16 ? dma_ct<bf16_t, false>(g, L, st) : dma_ct<float, false>(g, L, st);
 }
 
 }  // namespace lat

@@ -94,6 +94,7 @@ struct DmaLaunch {
   int splits, kps;
   float *partial, *rs_partial;
   int vec;  // 16-byte epilogue vectors allowed
+  bool reg; // rows start on any element: operands through registers
 };
 hipError_t gemm_dma(const GemmArgs& g, const DmaLaunch& L, hipStream_t st);
 size_t gemm_workspace(const GemmArgs& g);

@@ -37,6 +37,12 @@ SHAPES = {
     "bf16-odd-9-71-15": ("bf16", 130, (9, 71, 15), False),
     "bf16-odd-8-13-7": ("bf16", 65, (8, 13, 7), False),
     "bf16-odd-131-262-9": ("bf16", 300, (131, 262, 9), False),
+    # of these, products of few tiles (64x64 tiles through registers): 1 to 5 K
+    # steps, split weight gradients, edge tiles of 1 and 63 rows; at 3400 samples
+    # the forward (K = 1100) keeps the 128x128 kernel, the input gradient not
+    "bf16-odd-63-129-65": ("bf16", 129, (63, 129, 65), False),
+    "bf16-odd-193-257-127": ("bf16", 1025, (193, 257, 127), False),
+    "bf16-odd-1101-1217-9": ("bf16", 3400, (1101, 1217, 9), False),
     "bf16-odd-big-tiles": ("bf16", 3999, (1031, 4033, 9), False),
 }
 PADDED = {"bf16-padded-in-415", "bf16-padded-in-13", "bf16-mid-tiles-padded"}
