@@ -177,7 +177,9 @@ __device__ inline void fm_stage_w(const T* __restrict__ W, const FmDims& q, floa
   }
 }
 
-// tile t of [d, kk] = X^T M (M [nk, kk]) to Ps, rounded to T
+// tile t of [d, kk] = X^T M (M [nk, kk]) to Ps, rounded to T; columns past the
+// rank are zeros whatever X holds (its infinities times M's zero columns are
+// not, and dX contracts over all kk columns)
 template <typename T>
 __device__ inline void fm_p_tile(int t, const FmDims& q, const float* xs, const float* M, float* Ps) {
   const int lane = threadIdx.x & 63, kt = if_tiles(q.kk);
@@ -190,7 +192,7 @@ __device__ inline void fm_p_tile(int t, const FmDims& q, const float* xs, const 
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int a = a0 + frag_row(r);
-    if (a < q.d && c < q.kk) Ps[a * q.ldw + c] = ld_round<T>(acc[r]);
+    if (a < q.d && c < q.kk) Ps[a * q.ldw + c] = c < q.k ? ld_round<T>(acc[r]) : 0.f;
   }
 }
 
