@@ -97,6 +97,10 @@ __device__ inline void if_put(float* p, u32x4 x) {
   for (int q = 0; q < VE; q += 4) *reinterpret_cast<f32x4*>(p + q) = f32x4{f[q], f[q + 1], f[q + 2], f[q + 3]};
 }
 
+// a staged value back to T bit for bit (a conversion would quiet a bf16 NaN)
+__device__ inline void if_copy(float* p, float v) { *p = v; }
+__device__ inline void if_copy(bf16_t* p, float v) { *p = (bf16_t)(__float_as_uint(v) >> 16); }
+
 // A contiguous [rows, d] matrix of T to fp32 LDS rows of ldx by `threads`
 // threads (this one is t), 16-byte loads in rounds of U (all of a round in
 // flight together; d a multiple of 16).
@@ -222,7 +226,7 @@ __global__ __launch_bounds__(FM_F32_FWD_THREADS) void fm_fwd_f32_kernel(const T*
     __syncthreads();
     T* ob = out + (int64_t)b * ostride;
     if (emit0) {
-      for (int a = threadIdx.x; a < q.d; a += NT) st(ob + a, xs[a]);
+      for (int a = threadIdx.x; a < q.d; a += NT) if_copy(ob + a, xs[a]);
       ob += q.d;
     }
     for (int t = w; t < if_tiles(q.n) * kt; t += NT / 64) {
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(256) void dot_fwd_f32_kernel(const T* __restrict__ 
   const int off = emit0 ? d : 0;
   if (emit0)
     for (int e = threadIdx.x; e < cnt * d; e += 256)
-      st(out + (int64_t)(b0 + e / d) * ostride + e % d, if_smem[(e / d) * n * ldx + e % d]);
+      if_copy(out + (int64_t)(b0 + e / d) * ostride + e % d, if_smem[(e / d) * n * ldx + e % d]);
   const int nt = if_tiles(n), zt = nt * (nt + 1) / 2;
   for (int t = w; t < cnt * zt; t += 4) {
     const int sm = t / zt;

@@ -1,6 +1,6 @@
 """Non-finite values through the interactions: an infinite embedding value
 reaches exactly the outputs it belongs to, as an infinity, whatever padding a
-kernel adds to the rank or the rows."""
+kernel adds to the rank or the rows, and slot 0 is copied bit for bit."""
 import pytest
 import torch
 
@@ -34,3 +34,19 @@ def test_fm_infinity(dtype, k):
     assert torch.equal(_pattern(out), _pattern(torch.cat([x[:, 0], (x @ P).view(B, -1)], 1)))
     assert torch.equal(_pattern(dX), _pattern(G @ P.transpose(1, 2).contiguous() + w @ dP.transpose(1, 2).contiguous()))
     assert torch.equal(_pattern(dW), _pattern((x @ dP).sum(0)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,n,d", [("dot", 9, 32), ("dot", 40, 256), ("fm", 9, 32), ("dot", 9, 64)])
+def test_slot0_is_a_copy(kind, n, d):
+    """Every bf16 bit pattern, NaNs with and without the quiet bit among them."""
+    from paper_2512_09200_amd import api
+    print(f"[nonfinite] slot 0 {kind} n={n} d={d}", flush=True)
+    B, k = 65536 // d, 16
+    X = torch.ones((B, n, d), dtype=torch.bfloat16, device=DEV)
+    X[:, 0] = torch.arange(65536, device=DEV).to(torch.int16).view(torch.bfloat16).view(B, d)
+    out = torch.zeros((B, d + (n * (n - 1) // 2 if kind == "dot" else n * k)), dtype=torch.bfloat16, device=DEV)
+    W = torch.ones((n, k), dtype=torch.bfloat16, device=DEV) if kind == "fm" else None
+    api.lattice_interact_fwd(kind, X, out, True, fm_W=W)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:, :d].contiguous().view(torch.int16), X[:, 0].contiguous().view(torch.int16))
