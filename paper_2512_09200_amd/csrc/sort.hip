@@ -14,6 +14,7 @@
 // implemented here from its description; tiles take their ids in the order
 // they start, so every tile looked back at is running and publishes without
 // waiting).
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -83,37 +84,73 @@ __device__ inline int seg_len(const int32_t* __restrict__ offsets, int f, int B)
 }
 __device__ inline int seg_tiles(int len) { return (len + SORT_TILE - 1) / SORT_TILE; }
 
+// First tile of every segment ([F]: all tiles), one block.  Thread t takes the
+// features [t per, (t + 1) per).
+__global__ __launch_bounds__(1024) void seg_base_kernel(const int32_t* __restrict__ offsets, int F, int B,
+                                                        int* __restrict__ tile_base) {
+  __shared__ int lds[1024 / 64];
+  const int per = (F + 1023) / 1024;
+  const int lo = threadIdx.x * per < F ? threadIdx.x * per : F, hi = lo + per < F ? lo + per : F;
+  int sum = 0;
+#pragma unroll 4
+  for (int f = lo; f < hi; ++f) sum += seg_tiles(seg_len(offsets, f, B));
+  int total;
+  int run = block_exclusive_scan(sum, lds, &total);
+#pragma unroll 4
+  for (int f = lo; f < hi; ++f) {
+    tile_base[f] = run;
+    run += seg_tiles(seg_len(offsets, f, B));
+  }
+  if (threadIdx.x == 0) tile_base[F] = total;
+}
+
 // Everything the passes need before the digit counts, in one launch (a scan of
 // the tile counts, a tile map and two fills cost more in launches than in
 // work): a thread per bag.  A block adds up the tiles of the features before
-// its first bag's (F loads spread over the block), so no block waits for
-// another.
+// its first bag's itself (spread over the block), so no block waits for
+// another, and scans those of its own bags' features (at most 256); where that
+// is too much to add up in every block, seg_base_kernel has run before
+// (BASED).
 //   tile_base[f]  first tile of segment f ([F]: all tiles)
 //   tile_seg[t]   segment of tile t
 //   tile_bag0[t]  first bag of tile t: every non-empty bag writes its index to
 //                 the tiles that start inside it
-//   zero          cleared
+//   zero          cleared (blocks past the last bag only clear)
+template <bool BASED>
 __global__ __launch_bounds__(256) void seg_prep_kernel(const int32_t* __restrict__ offsets, int F, int B,
                                                        int* __restrict__ tile_base, int* __restrict__ tile_seg,
                                                        int* __restrict__ tile_bag0, int* __restrict__ zero,
                                                        int nzero) {
-  __shared__ int red[4];
-  const int64_t bag0 = (int64_t)blockIdx.x * 256, bag = bag0 + threadIdx.x;
+  __shared__ int red[4], own[256];
+  const int64_t bag0 = (int64_t)blockIdx.x * 256, bag = bag0 + threadIdx.x, bags = (int64_t)F * B;
   const int64_t nthreads = (int64_t)gridDim.x * 256;
   for (int64_t i = bag; i < nzero; i += nthreads) zero[i] = 0;
-  const int f0 = (int)(bag0 / B);
-  int base = 0;
-  for (int f = threadIdx.x; f < f0; f += 256) base += seg_tiles(seg_len(offsets, f, B));
+  if (bag0 >= bags) return;  // uniform per block
+  const int f0 = (int)(bag0 / B), f = (int)((bag < bags ? bag : bags - 1) / B);
+  int base;
+  if constexpr (BASED) {
+    base = tile_base[f];
+  } else {
+    int v = 0;
+    for (int q = threadIdx.x; q < f0; q += 256) v += seg_tiles(seg_len(offsets, q, B));
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) base += __shfl_xor(base, o, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = base;
-  __syncthreads();
-  base = red[0] + red[1] + red[2] + red[3];
-  if (bag >= (int64_t)F * B) return;
-  const int f = (int)(bag / B), b = (int)(bag - (int64_t)f * B);
-  for (int q = f0; q < f; ++q) base += seg_tiles(seg_len(offsets, q, B));
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    base = red[0] + red[1] + red[2] + red[3];
+    // the features of the block's bags: f0 .. f0 + 255 at most
+    const int64_t q = f0 + (int64_t)threadIdx.x;
+    const int mine = q < F && q * B < bag0 + 256 ? seg_tiles(seg_len(offsets, (int)q, B)) : 0;
+    __syncthreads();
+    int total;
+    own[threadIdx.x] = block_exclusive_scan(mine, red, &total);
+    __syncthreads();
+    base += own[f - f0];
+  }
+  if (bag >= bags) return;
+  const int b = (int)(bag - (int64_t)f * B);
   const int nt = seg_tiles(seg_len(offsets, f, B));
-  if (b == 0) {
+  if (!BASED && b == 0) {
     tile_base[f] = base;
     if (f == F - 1) tile_base[F] = base + nt;
   }
@@ -405,8 +442,18 @@ hipError_t radix_sort_segments(const int32_t* indices, int64_t n, const int32_t*
 
   // cleared: the digit counts and tile id counters (ghist and tile_ctr are adjacent)
   const int nzero = MAX_PASSES * F * (RADIX + CTR_STRIDE);
-  seg_prep_kernel<<<cdiv((int64_t)F * B, 256), 256, 0, s>>>(offsets, F, B, tile_base, tile_seg, tile_bag0, ghist,
-                                                           nzero);
+  const int64_t prep_blocks = std::max<int64_t>(cdiv((int64_t)F * B, 256), cdiv(nzero, 4096));
+  // The blocks' own sums read F * F * B / 512 tile counts in all; a launch that
+  // adds them up once costs about 4 us: at 64 features x 8192 samples (65K
+  // counts) the two take the same time, at 96 x 8192 (147K) the launch saves 2
+  // us of 264, at 256 x 8192 7 of 309, at 2000 x 4096 (32M) 110 of 900.
+  if ((int64_t)F * F * B > (int64_t)1 << 26) {
+    seg_base_kernel<<<1, 1024, 0, s>>>(offsets, F, B, tile_base);
+    LAT_LAUNCH_CHECK();
+    seg_prep_kernel<true><<<prep_blocks, 256, 0, s>>>(offsets, F, B, tile_base, tile_seg, tile_bag0, ghist, nzero);
+  } else {
+    seg_prep_kernel<false><<<prep_blocks, 256, 0, s>>>(offsets, F, B, tile_base, tile_seg, tile_bag0, ghist, nzero);
+  }
   LAT_LAUNCH_CHECK();
   radix_hist_all_kernel<<<tmax, SORT_THREADS, 0, s>>>(indices, offsets, row_base, F, B, tile_base,
                                                       tile_seg, passes, dbits, tmax, ghist, state);
