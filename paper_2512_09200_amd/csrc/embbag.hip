@@ -560,17 +560,15 @@ struct SegWave {
       if constexpr (FULL) {
         xf[i].w[0] = __builtin_amdgcn_raw_buffer_load_b32(dXr, lane_b, xr, 0);
       } else {
-        if (active) xf[i].load(reinterpret_cast<const DT*>(dXb + (uint32_t)xr + lane_b));
+        xf[i].load(reinterpret_cast<const DT*>(dXb + (uint32_t)xr + lane_b));
       }
       if (SGD && ((cm >> i) & 1)) {
         const int er_r = __builtin_amdgcn_readlane(erow, r);
-        if (FULL || active) {
-          if constexpr (EBUF) {
-            buf_load<ENB>(ef[i].w, er, lane_e, er_r);
-          } else {
-            const char* p = reinterpret_cast<const char*>(E) + (int64_t)er_r * erow_bytes + lane_e;
-            ef[i].load_nt(reinterpret_cast<const ET*>(p));
-          }
+        if constexpr (EBUF) {
+          buf_load<ENB>(ef[i].w, er, lane_e, er_r);
+        } else {
+          const char* p = reinterpret_cast<const char*>(E) + (int64_t)er_r * erow_bytes + lane_e;
+          ef[i].load_nt(reinterpret_cast<const ET*>(p));
         }
       }
     }
@@ -738,8 +736,11 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(
   w.dim = dim;
   w.col = lane * W::EPL;
   w.active = w.col < dim;
-  w.lane_b = lane * BPL;
-  w.lane_e = w.col * (int)sizeof(ET);
+  // lanes past a row's end load its first bytes, which nobody uses: under a
+  // condition each load's result would be merged with the register's old
+  // value, for which the compiler waits load by load
+  w.lane_b = w.active ? lane * BPL : 0;
+  w.lane_e = w.active ? w.col * (int)sizeof(ET) : 0;
   w.erow_bytes = (int64_t)dim * (int64_t)sizeof(ET);
   w.dXb = reinterpret_cast<const char*>(dX);
   w.dXr = __builtin_amdgcn_make_buffer_rsrc(
