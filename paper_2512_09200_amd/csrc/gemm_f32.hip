@@ -105,12 +105,13 @@ __device__ inline f32x4 f32_frag(const float* S, int r0, int ks, int lane) {
   return v;
 }
 
-// the wave's 32 k of a step from kw on
-template <bool TA, bool TB>
-__device__ inline void f32_step(const float* As, const float* Bs, int wm, int wn, int kw, int lane,
+// the wave's 32 k of a step from kw on (SHORT: those below K)
+template <bool TA, bool TB, bool SHORT>
+__device__ inline void f32_step(const float* As, const float* Bs, int wm, int wn, int kw, int K, int lane,
                                 f32x16& acc) {
 #pragma unroll
   for (int ks = 0; ks < FK / 2; ks += 8) {
+    if (SHORT && ks >= K) break;  // uniform
     const f32x4 a = f32_frag<TA>(As, wm * 32, kw + ks, lane), b = f32_frag<TB>(Bs, wn * 32, kw + ks, lane);
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
@@ -120,7 +121,11 @@ __device__ inline void f32_step(const float* As, const float* Bs, int wm, int wn
 // grid: x = M tiles * N tiles (renumbered per XCD), z = split.  partial: fp32
 // split partials [split][M][N] (splits > 1).  rowsum (TA only): sums of A over
 // k by the blocks of the first N tile, to rs_partial[split][m] when split.
-template <bool TA, bool TB, bool WIDE>
+// SHORT: K <= 32, one step of which only group 0 has a part and only the k
+// below K are multiplied (a 13-wide input layer: 30000 x 2048 outputs 147 ->
+// 102 us, the step's other 48 k being zeros; in the general kernel the bound
+// costs every product 5%).
+template <bool TA, bool TB, bool WIDE, bool SHORT>
 __global__ __launch_bounds__(F_THREADS) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda,
                                                        const float* __restrict__ Bm, int64_t ldb,
                                                        float* __restrict__ C, int64_t ldc, int M, int N,
@@ -168,18 +173,24 @@ __global__ __launch_bounds__(F_THREADS) void gemm_f32_kernel(const float* __rest
   };
   load(0);
   stage(0);
-  load(1);
-  __syncthreads();
-  // one step per iteration and no unrolling: most calls run a handful of
-  // steps, and a larger body costs more in instruction fetches than the loop
-  // saves.  Loads past the range read zeros (or values that are masked).
-#pragma unroll 1
-  for (int t = 0; t < steps; ++t) {
-    const float* S = smem + (t & 1) * 2 * F_STAGE;
-    f32_step<TA, TB>(S, S + F_STAGE, wm, wn, kg * (FK / 2), lane, acc);
-    stage(t + 1);
-    load(t + 2);
+  if constexpr (SHORT) {
     __syncthreads();
+    if (kg == 0) f32_step<TA, TB, true>(smem, smem + F_STAGE, wm, wn, 0, K, lane, acc);
+    __syncthreads();
+  } else {
+    load(1);
+    __syncthreads();
+    // one step per iteration and no unrolling: most calls run a handful of
+    // steps, and a larger body costs more in instruction fetches than the loop
+    // saves.  Loads past the range read zeros (or values that are masked).
+#pragma unroll 1
+    for (int t = 0; t < steps; ++t) {
+      const float* S = smem + (t & 1) * 2 * F_STAGE;
+      f32_step<TA, TB, false>(S, S + F_STAGE, wm, wn, kg * (FK / 2), K, lane, acc);
+      stage(t + 1);
+      load(t + 2);
+      __syncthreads();
+    }
   }
   if (rs_on) {
     // thread: rows 4 (tid % 16) .. +3 over its k class; the classes of a row
@@ -283,8 +294,15 @@ static hipError_t gemm_f32_launch(const GemmArgs& g, float* ws, hipStream_t st) 
     kern<<<grid, F_THREADS, 0, st>>>((const float*)g.A, g.lda, (const float*)g.B, g.ldb, (float*)g.C, g.ldc, g.M, g.N,
                                g.K, kps, partial, epi, g.rowsum, rs_partial);
   };
-  if (wide) launch(gemm_f32_kernel<TA, TB, true>);
-  else launch(gemm_f32_kernel<TA, TB, false>);
+  if constexpr (!TA) {
+    if (!wide && g.K <= FK / 2) {
+      launch(gemm_f32_kernel<TA, TB, false, true>);
+      LAT_LAUNCH_CHECK();
+      return hipSuccess;  // (only a weight gradient is split)
+    }
+  }
+  if (wide) launch(gemm_f32_kernel<TA, TB, true, false>);
+  else launch(gemm_f32_kernel<TA, TB, false, false>);
   LAT_LAUNCH_CHECK();
   if (splits > 1) {
     splitk_reduce_kernel<float><<<cdiv((int64_t)g.M * g.N, 256), 256, 0, st>>>(
