@@ -2,7 +2,9 @@
 // (Section 3.3.2): dot-product Gram (strict upper triangle) and the
 // factorization-machine block O_b = X_b (X_b^T W), forward and backward.
 //
-// These kernels stage one sample's vectors in LDS as fp32 and compute with
+// The scalar kernels of the shapes that neither the bf16 nor the fp32 MFMA
+// kernels take, and of those that are too small for the latter (the rules
+// below).  They stage one sample's vectors in LDS as fp32 and compute with
 // fp32 FMAs; storage rounding happens exactly where the products are stored
 // (P = X^T W and the output O for FM; the pair values for DOT), matching the
 // precision policy of the whole step.  The FM weight gradient is summed per
@@ -192,10 +194,31 @@ static hipError_t set_lds(const void* fn, size_t bytes) {
   return hipSuccess;
 }
 
+// Where the scalar kernels stay ahead of the fp32 MFMA ones, which spend whole
+// 32 x 32 tiles (and one wave's chain of MFMAs) on them.  DOT: few rows, or a
+// second tile's first rows at a small d.  8192 samples, scalar / MFMA: forward
+// n = 9 16 / 18 us (d = 96), 16 at 68 / 55 (d = 256), 33 x 16 20 / 23, 33 x 32
+// 35 / 31; backward n = 2 13 / 56 and 9 39 / 60 (d = 256), 14 at 23 / 22 and 18
+// at 30 / 32 (d = 64), 33 x 32 43 / 50, 40 x 32 57 / 52.
+static bool dot_fwd_scalar(int n, int d) { return n <= 12 || (n > 32 && n * n * d < 21000); }
+static bool dot_bwd_scalar(int n, int d) {
+  if (n <= 32) return 2 * n * n < 21 * ((n + 15) / 16 * 16) || n * n * d < 10000;
+  return n * n * d < 38000;
+}
+// FM forward: the scalar kernel's time grows with n d k (and with its LDS, from
+// n d = 8192 on), the MFMA kernel's hardly with the rank.  fp32, 8192 samples,
+// scalar / MFMA: 9 x 64 rank 16 26 / 71 us, 40 x 64 rank 16 86 / 92, 48 x 64
+// 100 / 92, 65 x 128 rank 8 231 / 165; bf16 33 x 32 rank 16 38 / 43, 48 x 32
+// 52 / 44, 20 x 256 rank 12 157 / 210, 27 x 256 rank 16 297 / 215.
+static bool fm_fwd_scalar(DType dt, int n, int d, int k) {
+  if (n * d > 8192 && k > 4) return false;
+  return dt == DT_F32 ? n * d * (k - 3) < 24576 + 128 * d : n * d * (k - 4) < 8192 + 160 * d;
+}
+
 hipError_t dot_fwd(DType dt, const void* X, int B, int n, int d, void* out, int64_t ostride,
                    int emit0, hipStream_t s) {
   if (B == 0) return hipSuccess;
-  if (dot_f32_supported(n, d, X))
+  if (!dot_fwd_scalar(n, d) && dot_f32_supported(n, d, X))
     return dot_f32(dt, true, X, B, n, d, out, ostride, emit0, nullptr, 0, nullptr, s);
   const size_t lds = (size_t)n * (d + 1) * 4;
   if (dt == DT_BF16) {
@@ -214,7 +237,7 @@ hipError_t dot_fwd(DType dt, const void* X, int B, int n, int d, void* out, int6
 hipError_t dot_bwd(DType dt, const void* X, int B, int n, int d, const void* dout,
                    int64_t dstride, int emit0, void* dX, hipStream_t s) {
   if (B == 0) return hipSuccess;
-  if (dot_f32_supported(n, d, X))
+  if (!dot_bwd_scalar(n, d) && dot_f32_supported(n, d, X))
     return dot_f32(dt, false, X, B, n, d, nullptr, 0, emit0, dout, dstride, dX, s);
   const size_t lds = ((size_t)n * (d + 1) + (size_t)n * (n + 1)) * 4;
   if (dt == DT_BF16) {
@@ -238,7 +261,8 @@ size_t fm_lds_bytes(int n, int d, int k) {
 hipError_t fm_fwd(DType dt, const void* X, const void* W, int B, int n, int d, int k, void* out,
                   int64_t ostride, int emit0, hipStream_t s) {
   if (B == 0) return hipSuccess;
-  if (fm_f32_supported(n, d, k, X)) return fm_fwd_f32(dt, X, W, B, n, d, k, out, ostride, emit0, s);
+  if (!fm_fwd_scalar(dt, n, d, k) && fm_f32_supported(n, d, k, X))
+    return fm_fwd_f32(dt, X, W, B, n, d, k, out, ostride, emit0, s);
   const size_t lds = ((size_t)n * (d + 1) + (size_t)n * k + (size_t)d * (k + 1)) * 4;
   if (dt == DT_BF16) {
     auto fn = fm_fwd_kernel<bf16_t>;
