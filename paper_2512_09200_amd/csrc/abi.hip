@@ -253,11 +253,9 @@ lattice_status lattice_embbag_bwd_noalloc(const lattice_tables* tables, const la
   if (bags->nnz > 0) REQUIRE(dX, "null dX");
   if ((int64_t)bags->batch * n_slots * tables->dim * (int64_t)esize(dx_dtype) > (int64_t)UINT32_MAX)
     FAIL(LATTICE_ERR_UNSUPPORTED, "dX larger than 4 GiB");
-  // the fine reduction ranges of small batches where the array has room for
-  // their partial sums (not with many thousands of features)
-  size_t need = embbag_bwd_workspace(bags->nnz, tables->dim, bags->num_features);
-  const bool coarse = need > (size_t)LATTICE_NOALLOC_SCRATCH_BYTES;
-  if (coarse) need = embbag_bwd_workspace(bags->nnz, tables->dim, bags->num_features, true);
+  static_assert(EMB_SHORT_RANGES_MAX_BYTES == LATTICE_NOALLOC_SCRATCH_BYTES,
+                "short reduction ranges never make a batch too large for the array");
+  const size_t need = embbag_bwd_workspace(bags->nnz, tables->dim, bags->num_features);
   if (need > (size_t)LATTICE_NOALLOC_SCRATCH_BYTES)
     FAIL(LATTICE_ERR_UNSUPPORTED,
          "the sparse gradient of %lld lookups (dim %d, %d features) needs %zu bytes of scratch; "
@@ -271,7 +269,7 @@ lattice_status lattice_embbag_bwd_noalloc(const lattice_tables* tables, const la
                     bags->num_features, bags->batch, bags->nnz, pool == LATTICE_POOL_MEAN, dX,
                     dt_of(dx_dtype), n_slots, first_slot, tables->dim, out->unique_rows,
                     out->seg_offsets, out->sorted_bags, out->num_unique, out->grad_rows,
-                    tables->data, dt_of(tables->dtype), lr, ws, strm(stream), coarse));
+                    tables->data, dt_of(tables->dtype), lr, ws, strm(stream)));
   return LATTICE_OK;
 }
 

@@ -303,18 +303,7 @@ constexpr int SEG_TILE = SEG_THREADS * SEG_ITEMS;
 // lookups of 128-byte rows 43 -> 26 us; above it they only add partial sums.
 constexpr int RANGE_SHIFT = 8, RANGE_SHIFT_SMALL = 6;
 constexpr int64_t RANGE_SMALL_MAX = (int64_t)1 << 21;
-static int range_shift(int64_t n, bool coarse) {
-  return !coarse && n <= RANGE_SMALL_MAX ? RANGE_SHIFT_SMALL : RANGE_SHIFT;
-}
-static int64_t range_count(int64_t n, bool coarse) {
-  const int s = range_shift(n, coarse);
-  return (n + ((int64_t)1 << s) - 1) >> s;
-}
-// the most ranges of any batch of at most n lookups
-static int64_t range_count_max(int64_t n, bool coarse) {
-  const int64_t c = range_count(n, coarse);
-  return coarse || n <= RANGE_SMALL_MAX ? c : std::max(c, range_count(RANGE_SMALL_MAX, false));
-}
+static int64_t range_count(int64_t n, int shift) { return (n + ((int64_t)1 << shift) - 1) >> shift; }
 
 // The keys of a tile's SEG_ITEMS stripes and of the positions before them,
 // loaded as straight-line code from clamped positions (n >= 1), so that all
@@ -877,9 +866,9 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // run bookkeeping: run starts per tile of keys and per group of tiles
 static int64_t run_words(int64_t n) { return (int64_t)cdiv(n, SEG_TILE) + cdiv(n, (int64_t)SEG_TILE * SEG_GROUP); }
 
-size_t embbag_bwd_workspace(int64_t nnz, int dim, int F, bool coarse) {
-  const int64_t n = nnz > 0 ? nnz : 1;
-  const int64_t ranges = range_count_max(n, coarse);
+// scratch of a batch of n lookups in ranges of 1 << shift
+static size_t bwd_bytes(int64_t n, int dim, int F, int shift) {
+  const int64_t ranges = range_count(n, shift);
   size_t s = 0;
   s += align256((size_t)n * 4);                        // sorted keys
   s += align256(radix_sort_segments_workspace(n, F));
@@ -887,6 +876,25 @@ size_t embbag_bwd_workspace(int64_t nnz, int dim, int F, bool coarse) {
   s += 2 * align256((size_t)ranges * 4);               // range_ubefore, part_uid
   s += align256((size_t)ranges * 2 * dim * 4);         // partial sums
   return s;
+}
+
+// A batch's ranges: the short ones for small batches, unless their partial
+// sums would take the scratch past EMB_SHORT_RANGES_MAX_BYTES (tens of
+// thousands of features).  A rule on the batch alone, so that every entry
+// point sums a batch in the same order.
+static int range_shift(int64_t n, int dim, int F) {
+  return n <= RANGE_SMALL_MAX && bwd_bytes(n, dim, F, RANGE_SHIFT_SMALL) <= EMB_SHORT_RANGES_MAX_BYTES
+             ? RANGE_SHIFT_SMALL : RANGE_SHIFT;
+}
+
+size_t embbag_bwd_workspace(int64_t nnz, int dim, int F) {
+  const int64_t n = nnz > 0 ? nnz : 1;
+  const int shift = range_shift(n, dim, F);
+  const size_t own = bwd_bytes(n, dim, F, shift);
+  if (shift == RANGE_SHIFT_SMALL) return own;
+  // a smaller batch may take short ranges, of at most this
+  const size_t small = bwd_bytes(std::min(n, RANGE_SMALL_MAX), dim, F, RANGE_SHIFT_SMALL);
+  return std::max(own, std::min(small, EMB_SHORT_RANGES_MAX_BYTES));
 }
 
 template <typename DT, typename ET>
@@ -948,9 +956,9 @@ struct EmbBwdWs {
   int *tile_counts, *range_ubefore, *part_uid;
   float* part;
 };
-static EmbBwdWs emb_bwd_ws(void* ws, int64_t nnz, int dim, int F, bool coarse) {
+static EmbBwdWs emb_bwd_ws(void* ws, int64_t nnz, int dim, int F) {
   const int64_t n = nnz > 0 ? nnz : 1;
-  const int64_t ranges = range_count(n, coarse);
+  const int64_t ranges = range_count(n, range_shift(n, dim, F));
   char* p = static_cast<char*>(ws);
   auto take = [&](size_t bytes) { char* q = p; p += align256(bytes); return q; };
   EmbBwdWs w;
@@ -966,7 +974,7 @@ static EmbBwdWs emb_bwd_ws(void* ws, int64_t nnz, int dim, int F, bool coarse) {
 hipError_t embbag_bwd_sort(const int64_t* row_base, int64_t max_local_rows, const int32_t* offsets,
                            const int32_t* indices, int F, int B, int64_t nnz, int dim,
                            int* unique_rows, int* seg_offsets, int* sorted_bags, int* num_unique,
-                           void* ws, hipStream_t s, void* const* ev, bool coarse) {
+                           void* ws, hipStream_t s, void* const* ev) {
   // ev (optional): 4 events, begin / end of the sort and of the run bookkeeping
   // (null entries are not recorded)
   auto record = [&](int i) -> hipError_t {
@@ -982,7 +990,7 @@ hipError_t embbag_bwd_sort(const int64_t* row_base, int64_t max_local_rows, cons
     return hipSuccess;
   }
   const int n = (int)nnz;
-  EmbBwdWs w = emb_bwd_ws(ws, nnz, dim, F, coarse);
+  EmbBwdWs w = emb_bwd_ws(ws, nnz, dim, F);
   hipError_t e = radix_sort_segments(indices, n, offsets, F, B, row_base, max_local_rows, w.skeys, sorted_bags,
                                      w.sort_ws, s);
   if (e != hipSuccess) return e;
@@ -997,7 +1005,7 @@ hipError_t embbag_bwd_sort(const int64_t* row_base, int64_t max_local_rows, cons
     seg_group_kernel<<<cdiv(tiles, SEG_GROUP), SEG_THREADS, 0, s>>>(w.tile_counts, tiles, groups);
     LAT_LAUNCH_CHECK();
   }
-  seg_write_kernel<<<tiles, SEG_THREADS, 0, s>>>(w.skeys, n, w.tile_counts, groups, range_shift(n, coarse), unique_rows,
+  seg_write_kernel<<<tiles, SEG_THREADS, 0, s>>>(w.skeys, n, w.tile_counts, groups, range_shift(n, dim, F), unique_rows,
                                                  seg_offsets, num_unique, w.range_ubefore);
   LAT_LAUNCH_CHECK();
   LAT_HIP_CHECK(record(3));
@@ -1008,7 +1016,7 @@ hipError_t embbag_bwd_apply(const int32_t* offsets, int F, int B, int64_t nnz, i
                             const void* dX, DType dxt, int n_slots, int first_slot, int dim,
                             const int* unique_rows, const int* seg_offsets, const int* sorted_bags,
                             float* grad_rows, void* E, DType et, float lr, void* ws, hipStream_t s,
-                            void* const* ev, bool coarse) {
+                            void* const* ev) {
   if (nnz == 0) {
     if (ev)
       for (int i = 0; i < 4; ++i)
@@ -1021,13 +1029,13 @@ hipError_t embbag_bwd_apply(const int32_t* offsets, int F, int B, int64_t nnz, i
               (long long)B * n_slots * dim * (dxt == DT_BF16 ? 2 : 4));
     return hipErrorInvalidValue;
   }
-  EmbBwdWs w = emb_bwd_ws(ws, nnz, dim, F, coarse);
+  EmbBwdWs w = emb_bwd_ws(ws, nnz, dim, F);
   void* Eupd = lr != 0.f ? E : nullptr;
 #define LAT_RED(DTT, ETT)                                                                       \
   return embbag_bwd_reduce<DTT, ETT>(w.skeys, sorted_bags, n, dX, B, n_slots, first_slot, dim,   \
                                      offsets, mean, w.range_ubefore, w.part, w.part_uid,          \
                                      seg_offsets, unique_rows,                                   \
-                                     grad_rows, Eupd, lr, range_shift(n, coarse), s, ev)
+                                     grad_rows, Eupd, lr, range_shift(n, dim, F), s, ev)
   if (dxt == DT_BF16 && et == DT_BF16) LAT_RED(bf16_t, bf16_t);
   if (dxt == DT_BF16 && et == DT_F32) LAT_RED(bf16_t, float);
   if (dxt == DT_F32 && et == DT_BF16) LAT_RED(float, bf16_t);
@@ -1039,14 +1047,12 @@ hipError_t embbag_bwd(const int64_t* row_base, int64_t max_local_rows, const int
                       const int32_t* indices, int F, int B, int64_t nnz, int mean,
                       const void* dX, DType dxt, int n_slots, int first_slot, int dim,
                       int* unique_rows, int* seg_offsets, int* sorted_bags, int* num_unique,
-                      float* grad_rows, void* E, DType et, float lr, void* ws, hipStream_t s,
-                      bool coarse) {
+                      float* grad_rows, void* E, DType et, float lr, void* ws, hipStream_t s) {
   hipError_t e = embbag_bwd_sort(row_base, max_local_rows, offsets, indices, F, B, nnz, dim,
-                                 unique_rows, seg_offsets, sorted_bags, num_unique, ws, s, nullptr,
-                                 coarse);
+                                 unique_rows, seg_offsets, sorted_bags, num_unique, ws, s, nullptr);
   if (e != hipSuccess) return e;
   return embbag_bwd_apply(offsets, F, B, nnz, mean, dX, dxt, n_slots, first_slot, dim, unique_rows,
-                          seg_offsets, sorted_bags, grad_rows, E, et, lr, ws, s, nullptr, coarse);
+                          seg_offsets, sorted_bags, grad_rows, E, et, lr, ws, s, nullptr);
 }
 
 // ---------------------------------------------------------------------------
