@@ -6,6 +6,8 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include "per_device.h"
+
 namespace lat {
 
 typedef uint16_t bf16_t;  // bf16 in memory: the upper 16 bits of an fp32
@@ -139,3 +141,19 @@ void set_error(const char* fmt, ...);
   } while (0)
 
 #define LAT_LAUNCH_CHECK() LAT_HIP_CHECK(hipGetLastError())
+
+namespace lat {
+
+// A kernel's limit of dynamic LDS, raised once on each device (function
+// attributes are a device's own); one LdsLimit per kernel.
+typedef PerDevice<hipError_t> LdsLimit;
+template <typename K>
+inline hipError_t lds_limit(K kern, size_t bytes, LdsLimit& lim) {
+  int dev = 0;
+  LAT_HIP_CHECK(hipGetDevice(&dev));
+  return lim.get(dev, [&] {
+    return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  });
+}
+
+}  // namespace lat

@@ -15,7 +15,6 @@
 // Accumulation is fp32; the pair values and dX are rounded to bf16 once,
 // where they are stored.
 #include <algorithm>
-#include <mutex>
 
 #include "common.h"
 #include "kernels.h"
@@ -575,13 +574,8 @@ static hipError_t dot_bwd_launch(const void* X, int B, int n, const void* dout, 
                                  hipStream_t s) {
   auto kern = dot_bwd_mfma_kernel<NP, D>;
   const size_t lds = dot_bwd_lds(n, NP, D);
-  static std::once_flag once;
-  static hipError_t attr = hipSuccess;
-  std::call_once(once, [&] {
-    attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)dot_bwd_lds(NP, NP, D));
-  });
-  LAT_HIP_CHECK(attr);
+  static LdsLimit lim;
+  LAT_HIP_CHECK(lds_limit(kern, dot_bwd_lds(NP, NP, D), lim));
   const int per = (int)std::min<size_t>(dot_bwd_blocks(NP), (size_t)160 * 1024 / lds);
   kern<<<B < 256 * per ? B : 256 * per, DOT_THREADS, lds, s>>>((const bf16_t*)X, B, n, (const bf16_t*)dout, dstride,
                                                                emit0, (bf16_t*)dX);

@@ -31,7 +31,6 @@
 // starts every 128-k block from zero (two chained instructions) and adds
 // its result to the fp32 accumulator with an ordinary fp32 add: each block's
 // alignment is relative to its own 128 products only.
-#include <mutex>
 
 #include "common.h"
 #include "kernels.h"
@@ -534,17 +533,17 @@ hipError_t gemm_fp8(const uint8_t* A, int64_t lda, const float* sa, int sa_rowwi
   if (M <= 0 || N <= 0) return hipSuccess;
   const int grid = cdiv(M, F8M) * cdiv(N, F8N);
   const bool wide = lda >= (1 << 24) || ldb >= (1 << 24);
-  auto launch = [&](auto kern, auto* c, std::once_flag& once) {
-    std::call_once(once, [&] {
-      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FP8_GEMM_LDS);
-    });
+  auto launch = [&](auto kern, auto* c, LdsLimit& lim) -> hipError_t {
+    LAT_HIP_CHECK(lds_limit(kern, FP8_GEMM_LDS, lim));
     kern<<<grid, 256, FP8_GEMM_LDS, s>>>(A, lda, sa, sa_rowwise, B, ldb, sb, sb_rowwise, bias, c, ldc, M, N, K);
+    LAT_LAUNCH_CHECK();
+    return hipSuccess;
   };
 #define LAT_F8(CTT, RL, PR)                                                                       \
   do {                                                                                            \
-    static std::once_flag once[2];                                                                \
-    if (wide) launch(gemm_fp8_kernel<CTT, RL, PR, true>, (CTT*)C, once[1]);                       \
-    else launch(gemm_fp8_kernel<CTT, RL, PR, false>, (CTT*)C, once[0]);                           \
+    static LdsLimit limits[2];                                                                    \
+    if (wide) return launch(gemm_fp8_kernel<CTT, RL, PR, true>, (CTT*)C, limits[1]);              \
+    return launch(gemm_fp8_kernel<CTT, RL, PR, false>, (CTT*)C, limits[0]);                       \
   } while (0)
 #define LAT_F8P(CTT, RL) \
   do { if (fast_accum) LAT_F8(CTT, RL, false); else LAT_F8(CTT, RL, true); } while (0)
@@ -555,8 +554,6 @@ hipError_t gemm_fp8(const uint8_t* A, int64_t lda, const float* sa, int sa_rowwi
   }
 #undef LAT_F8P
 #undef LAT_F8
-  LAT_LAUNCH_CHECK();
-  return hipSuccess;
 }
 
 }  // namespace lat

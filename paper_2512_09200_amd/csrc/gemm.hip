@@ -48,7 +48,6 @@
 // 1 / sqrt(...) are stored for the backward.  The 8 columns of a thread
 // belong to one aligned 16-lane group per 128 columns, so the sum of squares
 // is a 16-lane butterfly.
-#include <mutex>
 #include <type_traits>
 
 #include "common.h"
@@ -1166,23 +1165,21 @@ static hipError_t gemm_big_launch(const GemmArgs& g, bool aligned, hipStream_t s
   Opnd b{(const bf16_t*)g.B, g.ldb, g.kseg, g.ksB};
   const int vec = epi_vec_ok(g);
   const dim3 grid(cdiv(g.N, BBN) * cdiv(g.M, BBM));
-  static std::once_flag once[2][2];
-  auto launch = [&](auto kern, auto* c, std::once_flag& of) {
-    std::call_once(of, [&] {
-      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GEMM_BIG_LDS);
-    });
+  static LdsLimit limits[2][2];
+  auto launch = [&](auto kern, auto* c, LdsLimit& lim) -> hipError_t {
+    LAT_HIP_CHECK(lds_limit(kern, GEMM_BIG_LDS, lim));
     kern<<<grid, NW * 64, GEMM_BIG_LDS, st>>>(a, b, c, g.ldc, g.M, g.N, g.K, epi, vec, g.rowsum);
+    LAT_LAUNCH_CHECK();
+    return hipSuccess;
   };
   const bool buf = aligned && gemm_use_buf(g);
   if (g.c_dt == DT_BF16) {
-    if (buf) launch(gemm_big_kernel<TA, TB, bf16_t, NW, NORM, true>, (bf16_t*)g.C, once[0][1]);
-    else launch(gemm_big_kernel<TA, TB, bf16_t, NW, NORM, false>, (bf16_t*)g.C, once[0][0]);
+    if (buf) return launch(gemm_big_kernel<TA, TB, bf16_t, NW, NORM, true>, (bf16_t*)g.C, limits[0][1]);
+    return launch(gemm_big_kernel<TA, TB, bf16_t, NW, NORM, false>, (bf16_t*)g.C, limits[0][0]);
   } else {
-    if (buf) launch(gemm_big_kernel<TA, TB, float, NW, NORM, true>, (float*)g.C, once[1][1]);
-    else launch(gemm_big_kernel<TA, TB, float, NW, NORM, false>, (float*)g.C, once[1][0]);
+    if (buf) return launch(gemm_big_kernel<TA, TB, float, NW, NORM, true>, (float*)g.C, limits[1][1]);
+    return launch(gemm_big_kernel<TA, TB, float, NW, NORM, false>, (float*)g.C, limits[1][0]);
   }
-  LAT_LAUNCH_CHECK();
-  return hipSuccess;
 }
 
 // aligned: rows of both operands on 16 bytes; any: both may start on any element
@@ -1227,22 +1224,23 @@ static hipError_t gemm_bf16_launch(const GemmArgs& g, bool aligned, bool any, fl
   Opnd a{(const bf16_t*)g.A, g.lda, g.kseg, g.ksA};
   Opnd b{(const bf16_t*)g.B, g.ldb, g.kseg, g.ksB};
   // The kernels use 72 KiB of dynamic LDS (above the 64 KiB default limit).
-  static std::once_flag once[2][2];
-  auto launch = [&](auto kern, auto* c, std::once_flag& of) {
-    std::call_once(of, [&] {
-      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GEMM_LDS);
-    });
+  static LdsLimit limits[2][2];
+  auto launch = [&](auto kern, auto* c, LdsLimit& lim) -> hipError_t {
+    LAT_HIP_CHECK(lds_limit(kern, GEMM_LDS, lim));
     kern<<<grid, 256, GEMM_LDS, st>>>(a, b, c, g.ldc, g.M, g.N, g.K, kps, partial, epi, g.sA, g.sB, g.sC,
                                       batched, vec, g.rowsum, rs_partial, grp);
+    LAT_LAUNCH_CHECK();
+    return hipSuccess;
   };
+  hipError_t e;
   if (g.c_dt == DT_BF16) {
-    if (buf) launch(gemm_bf16_kernel<TA, TB, VA, VB, bf16_t, NORM, can_buf>, (bf16_t*)g.C, once[0][1]);
-    else launch(gemm_bf16_kernel<TA, TB, VA, VB, bf16_t, NORM, false>, (bf16_t*)g.C, once[0][0]);
+    if (buf) e = launch(gemm_bf16_kernel<TA, TB, VA, VB, bf16_t, NORM, can_buf>, (bf16_t*)g.C, limits[0][1]);
+    else e = launch(gemm_bf16_kernel<TA, TB, VA, VB, bf16_t, NORM, false>, (bf16_t*)g.C, limits[0][0]);
   } else {
-    if (buf) launch(gemm_bf16_kernel<TA, TB, VA, VB, float, NORM, can_buf>, (float*)g.C, once[1][1]);
-    else launch(gemm_bf16_kernel<TA, TB, VA, VB, float, NORM, false>, (float*)g.C, once[1][0]);
+    if (buf) e = launch(gemm_bf16_kernel<TA, TB, VA, VB, float, NORM, can_buf>, (float*)g.C, limits[1][1]);
+    else e = launch(gemm_bf16_kernel<TA, TB, VA, VB, float, NORM, false>, (float*)g.C, limits[1][0]);
   }
-  LAT_LAUNCH_CHECK();
+  if (e != hipSuccess) return e;
   return splits > 1 ? splitk_reduce(g, splits, ws, rs_partial, st) : hipSuccess;
 }
 

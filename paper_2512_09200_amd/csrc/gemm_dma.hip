@@ -27,8 +27,6 @@
 // (two to the banks' width) are moved to disjoint 64-byte bank groups by the
 // unit's XOR with 4 ((k >> 1) & 1).  The permutation is made by the lanes'
 // global addresses, inside one row's 128 bytes.
-#include <mutex>
-
 #include "common.h"
 #include "gemm_epi.h"
 #include "kernels.h"
@@ -346,12 +344,8 @@ template <bool TA, bool TB, typename CT, bool REG>
 static hipError_t dma_launch(const GemmArgs& g, const DmaLaunch& L, hipStream_t st) {
   auto kern = gemm_dma_kernel<TA, TB, CT, REG>;
   constexpr size_t lds = REG ? DMA_LDS / 2 : DMA_LDS;  // two stages, four
-  static std::once_flag once;
-  static hipError_t attr = hipSuccess;
-  std::call_once(once, [&] {
-    attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  });
-  LAT_HIP_CHECK(attr);
+  static LdsLimit lim;
+  LAT_HIP_CHECK(lds_limit(kern, lds, lim));
   const dim3 grid((unsigned)((int64_t)cdiv(g.N, DT) * cdiv(g.M, DT)), 1, L.splits);
   kern<<<grid, D_THREADS, lds, st>>>((const bf16_t*)g.A, g.lda, (const bf16_t*)g.B, g.ldb, (CT*)g.C, g.ldc, g.M,
                                          g.N, g.K, L.kps, L.partial, make_epi(g), L.vec, g.rowsum, L.rs_partial);

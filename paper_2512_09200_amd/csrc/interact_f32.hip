@@ -25,8 +25,6 @@
 // over n or the rank run to the next multiple of 16 over zeroed rows and
 // columns; rows and columns of a tile past the matrix repeat its last one and
 // are not stored.
-#include <mutex>
-
 #include "common.h"
 #include "kernels.h"
 #include "mfma_tile.h"
@@ -358,16 +356,6 @@ bool fm_f32_supported(int n, int d, int k, const void* X) {
   return ((uintptr_t)X & 15) == 0 && fm_f32_bwd_lds(fm_dims(n, d, k)) <= IF_LDS_MAX;
 }
 
-// dynamic LDS of up to the whole 160 KB (once per kernel)
-template <typename K>
-static hipError_t if_lds_limit(K kern, std::once_flag& once) {
-  hipError_t e = hipSuccess;
-  std::call_once(once, [&] {
-    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, IF_LDS_MAX);
-  });
-  return e;
-}
-
 // resident blocks: what the LDS holds on each of 256 compute units, at most `most`
 static int if_blocks(int B, size_t lds, int most) {
   const int per = (int)(IF_LDS_MAX / lds) < most ? (int)(IF_LDS_MAX / lds) : most;
@@ -377,8 +365,8 @@ static int if_blocks(int B, size_t lds, int most) {
 template <typename T>
 static hipError_t fm_fwd_f32_t(const void* X, const void* W, int B, int n, int d, int k, void* out, int64_t ostride,
                                int emit0, hipStream_t s) {
-  static std::once_flag once;
-  LAT_HIP_CHECK(if_lds_limit(fm_fwd_f32_kernel<T>, once));
+  static LdsLimit lim;
+  LAT_HIP_CHECK(lds_limit(fm_fwd_f32_kernel<T>, IF_LDS_MAX, lim));
   const FmDims q = fm_dims(n, d, k);
   const size_t lds = fm_f32_fwd_lds(q);
   fm_fwd_f32_kernel<T><<<if_blocks(B, lds, 4), FM_F32_FWD_THREADS, lds, s>>>((const T*)X, (const T*)W, q, B, (T*)out,
@@ -390,8 +378,8 @@ static hipError_t fm_fwd_f32_t(const void* X, const void* W, int B, int n, int d
 template <typename T>
 static hipError_t fm_bwd_f32_t(const void* X, const void* W, int B, int n, int d, int k, const void* dout,
                                int64_t dstride, int emit0, void* dX, float* dW, float* part, hipStream_t s) {
-  static std::once_flag once;
-  LAT_HIP_CHECK(if_lds_limit(fm_bwd_f32_kernel<T>, once));
+  static LdsLimit lim;
+  LAT_HIP_CHECK(lds_limit(fm_bwd_f32_kernel<T>, IF_LDS_MAX, lim));
   const FmDims q = fm_dims(n, d, k);
   const size_t lds = fm_f32_bwd_lds(q);
   const int tiles = if_tiles(n) * if_tiles(k);  // <= 8
@@ -541,13 +529,13 @@ static hipError_t dot_f32_t(bool fwd, const void* X, int B, int n, int d, void* 
                             const void* dout, int64_t dstride, void* dX, hipStream_t s) {
   const int spb = dot_f32_spb(n);
   if (fwd) {
-    static std::once_flag once;
-    LAT_HIP_CHECK(if_lds_limit(dot_fwd_f32_kernel<T>, once));
+    static LdsLimit lim;
+    LAT_HIP_CHECK(lds_limit(dot_fwd_f32_kernel<T>, IF_LDS_MAX, lim));
     dot_fwd_f32_kernel<T><<<cdiv(B, spb), 256, (size_t)spb * n * (d + 4) * 4, s>>>((const T*)X, B, n, d, spb, (T*)out,
                                                                                   ostride, emit0);
   } else {
-    static std::once_flag once;
-    LAT_HIP_CHECK(if_lds_limit(dot_bwd_f32_kernel<T>, once));
+    static LdsLimit lim;
+    LAT_HIP_CHECK(lds_limit(dot_bwd_f32_kernel<T>, IF_LDS_MAX, lim));
     // large samples leave room for one block per compute unit: twice the waves
     const size_t lds = dot_f32_bwd_lds(n, d);
     dot_bwd_f32_kernel<T><<<cdiv(B, spb), lds > IF_LDS_MAX / 3 ? 512 : 256, lds, s>>>(
