@@ -52,6 +52,7 @@
 
 #include "common.h"
 #include "gemm_epi.h"
+#include "gemm_span.h"
 #include "kernels.h"
 #include "swishrn.h"
 
@@ -1101,21 +1102,11 @@ static bool gemm_use_big(const GemmArgs& g) {
   return 308 * big_waves * s < 200 * small_waves;
 }
 
-// Bytes from an operand's first element to the end of its last one (one
-// batch): R rows (or columns) of K, K-contiguous (rows of ld) or not.
-static int64_t operand_span(int64_t ld, int R, int K, bool mn) {
-  if (R <= 0 || K <= 0) return 0;
-  return mn ? ((int64_t)(K - 1) * ld + (R + 7) / 8 * 8) * 2 : ((int64_t)(R - 1) * ld + (K + 7) / 8 * 8) * 2;
-}
-// Buffer loaders: no K segmentation and both operands within 2 GiB,
-// counting the k rows the last steps may address past the range (up to 256,
-// the 64 x 64 kernel's loads three steps ahead: their byte offsets must stay
-// below 2^32, out of the resource's range, so that they read zero rather than
-// wrap back into it).
-static bool gemm_use_buf(const GemmArgs& g) {
-  const int64_t lim = (int64_t)1 << 31;
-  auto reach = [](int64_t ld, int R, int K, bool mn) { return operand_span(ld, R, K, mn) + (mn ? 320 * ld * 2 : 1024); };
-  return g.kseg == 0 && reach(g.lda, g.M, g.K, g.ta) < lim && reach(g.ldb, g.N, g.K, g.tb) < lim;
+// Buffer loaders: no K segmentation and both operands (of one batch) in reach
+// of the kernel's loads (ahead: its k past the range).
+static bool gemm_use_buf(const GemmArgs& g, int ahead) {
+  return g.kseg == 0 && operand_in_buffer(g.lda, g.M, g.K, g.ta, ahead) &&
+         operand_in_buffer(g.ldb, g.N, g.K, g.tb, ahead);
 }
 
 // The 64 x 64 kernel takes single products (not batched, grouped or with the
@@ -1134,7 +1125,8 @@ static bool gemm_use_buf(const GemmArgs& g) {
 // 226 -> 233; 320 blocks of K = 1024 151 -> 145; 512 and more, K over 1024:
 // 210 -> 217.
 static bool gemm_use_small(const GemmArgs& g, bool aligned) {
-  if (g.batch > 1 || g.ngroups > 0 || g.norm_gate || (g.rowsum && !g.ta) || !gemm_use_buf(g)) return false;
+  if (g.batch > 1 || g.ngroups > 0 || g.norm_gate || (g.rowsum && !g.ta) || !gemm_use_buf(g, BUF_AHEAD_DMA))
+    return false;
   const int64_t blocks = (int64_t)cdiv(g.M, GBM) * cdiv(g.N, GBN) * gemm_splits(g);
   return aligned ? blocks <= 160 : blocks < 256 || (blocks <= 384 && g.K <= 1024);
 }
@@ -1172,7 +1164,7 @@ static hipError_t gemm_big_launch(const GemmArgs& g, bool aligned, hipStream_t s
     LAT_LAUNCH_CHECK();
     return hipSuccess;
   };
-  const bool buf = aligned && gemm_use_buf(g);
+  const bool buf = aligned && gemm_use_buf(g, BUF_AHEAD);
   if (g.c_dt == DT_BF16) {
     if (buf) return launch(gemm_big_kernel<TA, TB, bf16_t, NW, NORM, true>, (bf16_t*)g.C, limits[0][1]);
     return launch(gemm_big_kernel<TA, TB, bf16_t, NW, NORM, false>, (bf16_t*)g.C, limits[0][0]);
@@ -1190,7 +1182,7 @@ static hipError_t gemm_bf16_launch(const GemmArgs& g, bool aligned, bool any, fl
     if (!small && gemm_use_big(g)) return gemm_big_launch<TA, TB, NORM>(g, aligned, st);
   }
   constexpr bool can_buf = VA && VB;
-  const bool buf = can_buf && aligned && gemm_use_buf(g);
+  const bool buf = can_buf && aligned && gemm_use_buf(g, BUF_AHEAD);
   // (64 x 64 tiles already fill the chip where an input gradient would be split)
   const int splits = small && !TA && (int64_t)cdiv(g.M, 64) * cdiv(g.N, 64) >= 128 ? 1 : gemm_splits(g);
   if (splits > 1 && !ws) {

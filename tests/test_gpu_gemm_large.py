@@ -58,3 +58,28 @@ def test_layer_with_input_over_2gib():
     assert_product("d_in (sampled rows)", d_in[ri], Dr @ Wn, np.abs(Dr) @ np.abs(Wn), N, us)
     del x, d_in
     torch.cuda.empty_cache()
+
+
+@pytest.mark.gpu
+def test_operand_rows_over_2_22_elements():
+    """A few k rows of 4.2M elements each: within the reach of the 64-k steps'
+    buffer loads, whose last step addresses 64 rows past the operand, and out of
+    that of loads further ahead.  The weight gradient's M-contiguous B and the
+    input gradient's; in float64 from the stored operands."""
+    from paper_2512_09200_amd import api
+    Bw, Kw, Nw = 9, 4_200_000, 8
+    print(f"[gemm-large] B={Bw} K={Kw} N={Nw}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(11)
+    x = torch.randn((Bw, Kw), device=DEV, generator=g).to(torch.bfloat16)
+    W = (torch.randn((Nw, Kw), device=DEV, generator=g) / np.sqrt(Kw)).to(torch.bfloat16)
+    L = [dict(W=W, b=torch.zeros(Nw, device=DEV), dW=torch.zeros((Nw, Kw), device=DEV), db=torch.zeros(Nw, device=DEV))]
+    y = torch.ones((Bw, Nw), dtype=torch.bfloat16, device=DEV)
+    gout = torch.randn((Bw, Nw), device=DEV, generator=g).to(torch.bfloat16)
+    d_in = torch.empty((Bw, Kw), dtype=torch.bfloat16, device=DEV)
+    api.lattice_mlp_heads_bwd(L, x, [y], gout, True, d_in=d_in)
+    torch.cuda.synchronize()
+    D, X, Wd = gout.double(), x.double(), W.double()
+    err = (L[0]["dW"].double() - D.t().contiguous() @ X).abs()
+    assert bool((err <= Bw * 2.0 ** -22 * (D.abs().t().contiguous() @ X.abs()) + 1e-30).all())
+    ref, mag = D @ Wd, D.abs() @ Wd.abs()
+    assert bool(((d_in.double() - ref).abs() <= Nw * 2.0 ** -22 * mag + 2.0 ** -8 * ref.abs() + 1e-30).all())
