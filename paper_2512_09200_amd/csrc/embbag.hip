@@ -776,12 +776,24 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(
 // first run, and a null table reads the partials in its place; neither value
 // is used), then the runs are finished one by one: each run's arithmetic is
 // that of a wave taking it alone.
-constexpr int FIX_U = 4;
+//
+// A run of more than `wave_max` partial sums (tables of a few rows: one row may
+// have most of a batch's lookups, in short ranges 64 to a partial sum) would
+// keep its wave at it long after the others, so the block's four waves take it
+// together, with 4 S streams and eight loads in flight each.  wave_max is at
+// least the block's ranges, so at most one such run starts in them.  983K
+// lookups of one row, d = 128: lookup and gradient 825 -> 247 us (with ranges of 256 and a wave
+// per run 283); of 32 rows 124 -> 106 (115).
+constexpr int FIX_U = 4, FIX_WAVE_MAX = 32;
 template <typename ET>
 __global__ __launch_bounds__(256) void seg_fixup_kernel(
-    const int* __restrict__ part_uid, int ranges, int per, const int* __restrict__ seg_offsets,
+    const int* __restrict__ part_uid, int ranges, int per, int wave_max, const int* __restrict__ seg_offsets,
     const int* __restrict__ unique_rows, const float* __restrict__ part, int dim,
     float* __restrict__ grad_rows, ET* __restrict__ E, float lr, int rshift) {
+  __shared__ int long_run[3];  // first range (-1: none), run id, partial sums
+  __shared__ f32x4 long_sum[4][64];
+  if (threadIdx.x == 0) long_run[0] = -1;
+  __syncthreads();
   const int lane = threadIdx.x & 63;
   const int CL = dim / 4;  // 4-column groups (dim % 8 == 0, dim <= 256)
   const int S = 64 / CL;   // streams
@@ -809,7 +821,7 @@ __global__ __launch_bounds__(256) void seg_fixup_kernel(
       }
 #pragma unroll
       for (int t = 0; t < FIX_U; ++t) {
-        Q[t] = ((seg_offsets[u[t] + 1] - 1) >> rshift) - c0[t] + 1;
+        Q[t] = __builtin_amdgcn_readfirstlane(((seg_offsets[u[t] + 1] - 1) >> rshift) - c0[t] + 1);
         erow[t] = E ? (int64_t)unique_rows[u[t]] * dim : 0;
       }
       // stream s's first partial sum (q = s; the run's first slot where the
@@ -827,6 +839,14 @@ __global__ __launch_bounds__(256) void seg_fixup_kernel(
 #pragma unroll
       for (int t = 0; t < FIX_U; ++t) {
         if (t >= cnt) break;  // wave-uniform
+        if (Q[t] > wave_max) {
+          if (lane == 0) {
+            long_run[0] = c0[t];
+            long_run[1] = u[t];
+            long_run[2] = Q[t];
+          }
+          continue;
+        }
         f32x4 a = {0.f, 0.f, 0.f, 0.f};
         if (act && s < Q[t]) {
           a += a0[t];
@@ -857,6 +877,45 @@ __global__ __launch_bounds__(256) void seg_fixup_kernel(
           }
         }
       }
+    }
+  }
+  __syncthreads();
+  const int lc = long_run[0], lu = long_run[1], lQ = long_run[2];
+  if (lc < 0) return;  // uniform per block
+  const int w = threadIdx.x >> 6;
+  f32x4 a = {0.f, 0.f, 0.f, 0.f};
+  if (act) {
+#pragma unroll 1
+    for (int q = w * S + s; q < lQ; q += 32 * S) {
+      f32x4 v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {  // past the last one: this round's first, not added
+        const int p = q + 4 * S * k < lQ ? q + 4 * S * k : q;
+        const int64_t slot = p == 0 ? (int64_t)lc * 2 + 1 : (int64_t)(lc + p) * 2;
+        v[k] = *reinterpret_cast<const f32x4*>(part + slot * dim + cq * 4);
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (q + 4 * S * k < lQ) a += v[k];
+    }
+  }
+  f32x4 t4 = {0.f, 0.f, 0.f, 0.f};
+  for (int ss = 0; ss < S; ++ss) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t4[e] += __shfl(a[e], ss * CL + cq, 64);
+  }
+  if (s == 0) long_sum[w][cq] = t4;
+  __syncthreads();
+  if (threadIdx.x < CL) {
+    const int64_t erow = E ? (int64_t)unique_rows[lu] * dim : 0;
+    t4 = long_sum[0][cq];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) t4 += long_sum[k][cq];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int c = cq * 4 + e;
+      if (grad_rows) grad_rows[(int64_t)lu * dim + c] = t4[e];
+      if (E) st(E + erow + c, ld(E + erow + c) - lr * t4[e]);
     }
   }
 }
@@ -942,8 +1001,9 @@ static hipError_t embbag_bwd_reduce(const int* skeys, const int* sbags, int n, c
   // every wave resident (5 blocks of 4 waves per compute unit at the
   // kernel's 88-96 VGPRs), each with at least a round's worth of ranges
   const int per = std::max(FIX_U, cdiv(ranges, 5120));
-  seg_fixup_kernel<ET><<<cdiv(cdiv(ranges, per), 4), 256, 0, s>>>(part_uid, ranges, per, seg_offsets, unique_rows, part,
-                                                                 dim, grad_rows, (ET*)E, lr, rshift);
+  seg_fixup_kernel<ET><<<cdiv(cdiv(ranges, per), 4), 256, 0, s>>>(part_uid, ranges, per,
+                                                                 std::max(FIX_WAVE_MAX, 4 * per), seg_offsets,
+                                                                 unique_rows, part, dim, grad_rows, (ET*)E, lr, rshift);
   LAT_LAUNCH_CHECK();
   LAT_HIP_CHECK(record(3));
   return hipSuccess;
