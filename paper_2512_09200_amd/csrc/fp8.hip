@@ -439,22 +439,29 @@ __global__ __launch_bounds__(256, 2) void gemm_fp8_kernel(
   F8Op<WIDE> oa, ob;
   oa.init(A, lda, M, K, m0, w, lane);
   ob.init(Bm, ldb, N, K, n0, w, lane);
-  if (ktiles > 0) {
-    oa.issue(f8_smem, 0, w);
-    ob.issue(f8_smem + F8TILE, 0, w);
-  }
+  auto issue = [&](int kt) {
+    uint8_t* S = f8_smem + (kt & 1) * 2 * F8TILE;
+    oa.issue(S, kt * F8K, w);
+    ob.issue(S + F8TILE, kt * F8K, w);
+  };
+  // Both stages are free at the start: the first two steps' loads go out
+  // together.  One after the other, the start of a block's short chain waited
+  // twice for memory (16384 x 1024 x 1024 fast, quantisation included: 52.4 us,
+  // now 47.9; 49.7 when operands went through registers).
+  if (ktiles > 0) issue(0);
+  if (ktiles > 1) issue(1);
 #pragma unroll 1
   for (int kt = 0; kt < ktiles; ++kt) {
-    // this wave's loads of the step have landed and its LDS reads of the other
-    // stage returned; past the barrier everybody's have, so that stage is free
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    // this wave's loads of the step have landed (at step 0 the 8 of step 1 may be
+    // in flight) and its LDS reads of the other stage returned; past the barrier
+    // everybody's have, so that stage is free
+    if (kt == 0 && ktiles > 1) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     uint8_t* As = f8_smem + (kt & 1) * 2 * F8TILE;
     if (kt + 1 < ktiles) {
-      uint8_t* S = f8_smem + ((kt + 1) & 1) * 2 * F8TILE;
-      oa.issue(S, (kt + 1) * F8K, w);
-      ob.issue(S + F8TILE, (kt + 1) * F8K, w);
+      if (kt > 0) issue(kt + 1);
     } else if (K % F8K != 0 && (WIDE || K % 16 != 0)) {  // uniform
       f8_zero_tail<WIDE>(As, K % F8K);
       f8_zero_tail<WIDE>(As + F8TILE, K % F8K);

@@ -111,3 +111,25 @@ def test_linear_fp8_row_strides(K, fast):
     pad = api.lattice_linear_fp8_fwd(packed, sa, qw, sw, K, fast_accum=fast, out_dtype=torch.float32)
     torch.cuda.synchronize()
     assert torch.isfinite(ref).all() and torch.equal(got, ref) and torch.equal(pad, ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K", [100, 128, 240, 256, 300, 384, 400])
+@pytest.mark.parametrize("fast", [False, True], ids=["precise", "fast"])
+def test_linear_fp8_first_steps(K, fast):
+    """One to four K steps, whole and cut: the first two steps' loads are issued
+    together, the later ones a step ahead."""
+    from paper_2512_09200_amd import api
+    print(f"[fp8] K={K} fast_accum={fast}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(K)
+    M, N = 700, 260
+    x, w = torch.randn((M, K), device=DEV, generator=g), torch.randn((N, K), device=DEV, generator=g)
+    qa, sa = api.lattice_fp8_quantize(x)
+    qw, sw = api.lattice_fp8_quantize(w)
+    got = api.lattice_linear_fp8_fwd(qa, sa, qw, sw, K, fast_accum=fast, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    a, b = ofp8.quantize(x.cpu().numpy(), True), ofp8.quantize(w.cpu().numpy(), True)
+    zero = np.zeros(N, np.float32)
+    ref = ofp8.linear_fp8(*a, *b, zero, relu=False)
+    bound = ofp8.linear_fp8_bound(*a, *b, zero, fast_accum=fast) + 1e-37
+    assert np.all(np.abs(got.cpu().double().numpy() - ref) <= bound)
