@@ -393,7 +393,8 @@ static bool fm_uses_mfma(const lattice_interact_desc* d, int64_t stride = 8) {
   return d->dtype == LATTICE_BF16 && fm_mfma_supported(d->n, d->dim, d->rank) && stride % 8 == 0;
 }
 
-// DOT on MFMA: bf16, n <= 128, d in {64, 128}, X rows read with 4-byte loads
+// DOT on MFMA: bf16, n <= 128, d in {64, 128}, X on 4 bytes (its rows are read
+// in vectors of that alignment)
 static bool dot_uses_mfma(const lattice_interact_desc* d, const void* X) {
   return d->dtype == LATTICE_BF16 && dot_mfma_supported(d->n, d->dim) &&
          ((uintptr_t)X & 3) == 0;

@@ -2,8 +2,8 @@
 // deterministic row-coalesced gradient with an optional fused row-sparse SGD
 // update.
 //
-// Forward: one wavefront per 16 consecutive bags, walking their lookups one
-// table row per step (each lane holds a 4..16-byte slice of the row), with
+// Forward: one wavefront per 16 consecutive bags (4 in batches of fewer than
+// 65,536), walking their lookups one table row per step (each lane holds a 4..16-byte slice of the row), with
 // the rows of 8..32 lookups in flight at once; each bag is summed in position
 // order in fp32 and stored when it ends.
 //
@@ -14,15 +14,17 @@
 //              sorted by its local row and only the largest table's row bits
 //              need digit passes
 //   segments : run boundaries -> unique rows ascending, run offsets, and the
-//              run id before every 256-position range
-//   reduce   : one wave per range of 256 sorted occurrences; dX rows are
+//              run id before every reduction range
+//   reduce   : one wave per range of 256 sorted occurrences (64 in small
+//              batches); dX rows are
 //              gathered into registers chunk by chunk and summed by an
 //              in-register segmented scan in a fixed order, with the running
 //              sum carried from chunk to chunk.  Runs that start and end in
 //              the range are final (written to G and/or applied as SGD); a
 //              run cut by a range boundary leaves a partial sum
-//   fixup    : each run that crosses ranges sums its partials in range order
-// Work per wave is uniform whatever the Zipf skew of the rows.
+//   fixup    : each run that crosses ranges sums its partials in a fixed order
+//              (a block together where they are many)
+// Work per wave of the reduction is uniform whatever the Zipf skew of the rows.
 #include <algorithm>
 
 #include "common.h"
@@ -782,8 +784,8 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(
 // keep its wave at it long after the others, so the block's four waves take it
 // together, with 4 S streams and eight loads in flight each.  wave_max is at
 // least the block's ranges, so at most one such run starts in them.  983K
-// lookups of one row, d = 128: lookup and gradient 825 -> 247 us (with ranges of 256 and a wave
-// per run 283); of 32 rows 124 -> 106 (115).
+// lookups of one row, d = 128, lookup and gradient: 825 -> 247 us (283 with
+// ranges of 256 and a wave per run); of 32 rows 124 -> 106 (115).
 constexpr int FIX_U = 4, FIX_WAVE_MAX = 32;
 template <typename ET>
 __global__ __launch_bounds__(256) void seg_fixup_kernel(
