@@ -1475,6 +1475,9 @@ lattice_status lattice_step_plan(const lattice_model_desc* model, int32_t B, int
 
 }  // extern "C"
 
+// Lookups above which the step forks the sort after the interaction.
+constexpr int64_t LATE_SORT_NNZ = (int64_t)1 << 21;
+
 // The step (forward_only = false) or its forward alone (lattice_forward).
 static lattice_status step_impl(const lattice_model_desc* m, const lattice_batch_desc* batch,
                                 const lattice_step_opts* opts, void* ws, size_t ws_bytes,
@@ -1593,14 +1596,21 @@ static lattice_status step_impl(const lattice_model_desc* m, const lattice_batch
                     batch->bags.indices, m->num_features, B, m->pool == LATTICE_POOL_MEAN, X, dt,
                     n, s0, s));
   HIPRET(end(LATTICE_STAGE_EMBBAG_FWD));
-  // fork: the sort and run bookkeeping go to the side stream, overlapping
-  // the dense stages
-  if (side && !forward_only) {
-    HIPRET(hipEventRecord(side->fork_fwd, s));
-    HIPRET(hipStreamWaitEvent(side->s, side->fork_fwd, 0));
-    HIPRET(sparse_sort(side->s));
-    HIPRET(hipEventRecord(side->sorted, side->s));
-  }
+  // fork: the sort and run bookkeeping go to the side stream, overlapping the
+  // dense stages.  A large batch's passes fill the chip and would slow the
+  // interaction and the top MLP's forward, which the step waits for, while the
+  // sort is done long before its result is wanted: they start after the
+  // interaction.  10.5M lookups (large-embedding step) 1.311 -> 1.295 ms, 4.9M
+  // (multi-domain) 1.033 -> 1.025; 0.5M, whose step waits for the sort, 0.225 ->
+  // 0.25, so small batches fork here.
+  auto fork_sort = [&]() -> hipError_t {
+    HIP_TRY(hipEventRecord(side->fork_fwd, s));
+    HIP_TRY(hipStreamWaitEvent(side->s, side->fork_fwd, 0));
+    HIP_TRY(sparse_sort(side->s));
+    return hipEventRecord(side->sorted, side->s);
+  };
+  const bool sort_on_side = side && !forward_only, sort_late = nnz > LATE_SORT_NNZ;
+  if (sort_on_side && !sort_late) HIPRET(fork_sort());
   if (bottom_on_side) HIPRET(hipStreamWaitEvent(s, side->bottom_done, 0));
   else HIPRET(bottom_forward(s));
   // 3. interaction -> top input t = [X[:,0,:], interaction]
@@ -1615,6 +1625,7 @@ static lattice_status step_impl(const lattice_model_desc* m, const lattice_batch
   }
   HIPRET(interact_fwd_impl(&idesc, B, X, t, P.t_stride, at(L.interact), s));
   HIPRET(end(LATTICE_STAGE_INTERACT_FWD));
+  if (sort_on_side && sort_late) HIPRET(fork_sort());
   // 4. top MLP -> logits; 5. masked BCE.  bf16 models with at most 64 heads
   // run the last layer as the fused heads: its forward with the loss
   // partials, then dz, the loss and the last layer's input gradient (which
