@@ -1000,9 +1000,10 @@ static hipError_t embbag_bwd_reduce(const int* skeys, const int* sbags, int n, c
   LAT_LAUNCH_CHECK();
   LAT_HIP_CHECK(record(1));
   LAT_HIP_CHECK(record(2));
-  // every wave resident (5 blocks of 4 waves per compute unit at the
-  // kernel's 88-96 VGPRs), each with at least a round's worth of ranges
-  const int per = std::max(FIX_U, cdiv(ranges, 5120));
+  // every wave resident (5 or 6 blocks of 4 waves per compute unit), each with
+  // whole rounds of ranges: most ranges of a large batch end inside a run, and 9
+  // to a wave took a third round for one of them (40,969 ranges: 17.8 -> 16.5 us)
+  const int per = FIX_U * std::max(1, cdiv(ranges, FIX_U * 6144));
   seg_fixup_kernel<ET><<<cdiv(cdiv(ranges, per), 4), 256, 0, s>>>(part_uid, ranges, per,
                                                                  std::max(FIX_WAVE_MAX, 4 * per), seg_offsets,
                                                                  unique_rows, part, dim, grad_rows, (ET*)E, lr, rshift);
