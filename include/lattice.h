@@ -474,7 +474,8 @@ typedef enum {
  * may be disabled) that it uses to fork work from `stream` onto the side
  * stream and to join it back: the bottom MLP's forward is forked at the
  * step's start and runs beside the pooled lookups; the sort is forked after
- * the pooled lookups and overlaps the dense forward and backward; the bottom
+ * the pooled lookups (above 2^21 lookups, after the interaction) and overlaps
+ * the dense forward and backward; the bottom
  * MLP's backward is forked after the interaction backward and overlaps the
  * top MLP's weight gradients and the segmented reduction (which waits for
  * the sort), both on `stream`.  All work is still ordered

@@ -1451,8 +1451,8 @@ static lattice_status make_plan(const lattice_model_desc* m, int B, int64_t nnz,
 namespace {
 struct SideStream {
   hipStream_t s = nullptr;
-  // fork at the step's start, after the pooled lookups and after the
-  // interaction backward; join of the bottom MLP's forward, of the sort and
+  // fork at the step's start, after the pooled lookups (large batches: after
+  // the interaction) and after the interaction backward; join of the bottom MLP's forward, of the sort and
   // run bookkeeping and of the dense weight gradients
   hipEvent_t fork_start = nullptr, fork_fwd = nullptr, fork_bwd = nullptr;
   hipEvent_t bottom_done = nullptr, sorted = nullptr, done = nullptr;

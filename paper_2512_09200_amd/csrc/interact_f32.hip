@@ -11,11 +11,11 @@
 // four, one per wave) and its waves share the 32x32 output tiles; the FM
 // kernels stay resident, keep W in LDS and hold the next sample's X (and its
 // gradient) in registers while the current one is computed.
-// fp32, 2048 samples of 65 x 128 at rank 32: forward 49 us, backward with the
-// weight gradient 117 + 5 us (scalar kernels: 208, 1580 + 119 us); the matrix
-// cores are busy 43-46% of that, 19 and 48 us, a third of it on the tiles'
-// padding (65 rows as 96); what remains is the phases' barriers and LDS
-// latency at two waves per SIMD.
+// fp32, 2048 samples of 65 x 128 at rank 32, each kernel's own time: forward 50
+// us, backward with the weight gradient 118 + 5 us (scalar kernels: 208, 1580 +
+// 119 us), 162 us a forward and backward in a row of calls; the matrix cores
+// are busy 42-46% of that, a third of it on the tiles' padding (65 rows as 96);
+// what remains is the phases' barriers and LDS latency at two waves per SIMD.
 //
 // LDS layouts (floats): a matrix whose rows are read along the contraction
 // (16 bytes per lane) or across it (one row element per lane) alike has rows
